@@ -316,7 +316,7 @@ hla_status hla_create(const hla_config* c, hla_handle** out) {
   // padding entries of packed operands are never written afterwards and must read as zero
   if (st == HLA_OK && hd->path_ws_bytes > 0 && hipMemset(hd->path_ws, 0, hd->path_ws_bytes) != hipSuccess)
     st = HLA_ERR_HIP;
-  if (st == HLA_OK) st = hd->path == HLA_PATH_MFMA ? mfma_prepare_kernels(hd) : generic_prepare_kernels(hd);
+  if (st == HLA_OK) st = hd->path == HLA_PATH_MFMA ? mfma_prepare_kernels(hd) : generic_prepare_kernels(hd, nullptr);
   if (st == HLA_OK && hipDeviceSynchronize() != hipSuccess) st = HLA_ERR_HIP;
   if (st != HLA_OK) {
     free_all(hd);
@@ -655,6 +655,7 @@ hla_status hla_forward_static(const hla_config* config, int32_t B, int32_t H, in
           static_cast<uint32_t*>(hd->path_ws), words);
       if (hipGetLastError() != hipSuccess) return HLA_ERR_HIP;
     }
+    if (hd->path == HLA_PATH_GENERIC) HLA_TRY(generic_prepare_kernels(hd, s));  // after the fill: it writes tables there
     sl.cfg = c;
     sl.planned = true;
   }

@@ -1,13 +1,10 @@
-// Generic path: fp32 vector-ALU kernels over the literal d_phi^F feature tensor (no matrix
-// cores, no algebraic compression).  Serves fp32 I/O, unusual (F, d_phi) and acts as an
-// independent GPU cross-check of the MFMA path.  Throughput is not a goal here.
+// Generic path, common parts: feature import / export, the feature maps and their gradients on the
+// fp32 vector ALU, and the causal variant as a token-by-token scan over the literal d_phi^F feature
+// tensor (a cross-check of the matrix-core path; throughput is not a goal there).  The non-causal
+// operator of this path is hla_f32.hip.
 //
-// With the augmented state  Chat = [C | z]  ([D, d+1]) and augmented per-token rows
-// vhat_j = [v_j | 1], ghat_i = [dO_i/den_i | -<dO_i,o_i>/den_i] every step is one of three
-// shapes (Theorem 4.2 and its derivatives):
-//   accumulate : Chat  = sum_j T_j (x) yhat_j            (state; d state with T_q, ghat)
-//   contract   : out_i = T_i . Chat                       (query side; dV with T_k, dChat)
-//   dtensor    : dT_i  = Chat yhat_i, then the chain rule through the outer product
+// The scan uses the augmented state  Chat = [C | z]  ([D, d+1]) and augmented per-token rows
+// vhat_j = [v_j | 1], ghat_i = [dO_i/den_i | -<dO_i,o_i>/den_i].
 #include <cmath>
 
 #include "hla_handle.h"
@@ -16,11 +13,7 @@ namespace hla {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunk = 1024;      // tokens per partial state
-constexpr int kAccTile = 8;       // tokens staged per step of accumulate
-constexpr int kMaxRows = 128;     // accumulator rows per thread in accumulate: D*d/256 <= 128
-constexpr int kTokPerThread = 4;  // contract: tokens per thread
-constexpr int kDtTile = 8;        // dtensor: tokens per block
+constexpr int kChunk = 1024;      // tokens per table entry of the causal scan
 constexpr int kPhiTile = 16;      // feature maps: tokens per block
 constexpr int kWgTile = 8;        // weight gradients: tokens staged per step
 constexpr int kMaxF = 4;
@@ -430,147 +423,6 @@ hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
   return weight_grads_reduce(hd, static_cast<int>(nchunk), heads, 1.0f, 1.0f, 1.0f, 1.0f, s);
 }
 
-// ---- accumulate: partial Chat = sum over a chunk of tokens of T (x) yhat -----------------------
-// YIO = true : yhat_j = [V_j | 1] read from the caller's V (I/O dtype, strided)
-// YIO = false: yhat_i read from the dense fp32 scratch [th][d+1]
-// grid (chunks, H), block 256.  Thread (r, c): column c, rows r + k*R with R = 256/d.
-template <typename T, bool YIO>
-__global__ void k_accumulate(Geom g, const BlockEnt* __restrict__ chunks,
-                             const float* __restrict__ feat, bool query, View Y,
-                             const float* __restrict__ ydense, float* __restrict__ partial,
-                             int64_t state_stride) {
-  extern __shared__ float smem[];
-  const int d = g.d, D = g.D;
-  const int R = kThreads / d;
-  const int nrows = (D + R - 1) / R;
-  const int Dpad = nrows * R;
-  float* ts = smem;                    // [kAccTile][Dpad]
-  float* ys = ts + kAccTile * Dpad;    // [kAccTile][d+1]
-  float* fs = ys + kAccTile * (d + 1); // [kAccTile][nfeat]
-  const BlockEnt e = chunks[blockIdx.x];
-  const int h = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int c = tid % d, r = tid / d;
-  float acc[kMaxRows];
-#pragma unroll
-  for (int k = 0; k < kMaxRows; ++k) acc[k] = 0.0f;
-  float zacc = 0.0f;
-  for (int n0 = e.t0; n0 < e.t1; n0 += kAccTile) {
-    const int nt = min(kAccTile, e.t1 - n0);
-    __syncthreads();
-    for (int idx = tid; idx < kAccTile * g.nfeat; idx += kThreads) {
-      const int t = idx / g.nfeat;
-      fs[idx] = t < nt ? feat[g.th(e.b, h, n0 + t) * g.nfeat + idx % g.nfeat] : 0.0f;
-    }
-    for (int idx = tid; idx < kAccTile * (d + 1); idx += kThreads) {
-      const int t = idx / (d + 1), cc = idx % (d + 1);
-      float y = 0.0f;
-      if (t < nt) {
-        if (YIO)
-          y = cc < d ? to_float(Y.row<const T>(e.b, h, n0 + t)[cc]) : 1.0f;
-        else
-          y = ydense[g.th(e.b, h, n0 + t) * (d + 1) + cc];
-      }
-      ys[idx] = y;
-    }
-    __syncthreads();
-    for (int idx = tid; idx < kAccTile * Dpad; idx += kThreads) {
-      const int t = idx / Dpad, Di = idx % Dpad;
-      ts[idx] = Di < D ? outer_entry(fs + t * g.nfeat, query, Di, g.F, g.dphi) : 0.0f;
-    }
-    __syncthreads();
-    for (int t = 0; t < nt; ++t) {
-      const float yv = ys[t * (d + 1) + c];
-      const float* trow = ts + t * Dpad + r;
-#pragma unroll
-      for (int k = 0; k < kMaxRows; ++k)
-        if (k < nrows) acc[k] += trow[k * R] * yv;
-      if (tid < D) zacc += ts[t * Dpad + tid] * ys[t * (d + 1) + d];
-    }
-  }
-  float* out = partial + (static_cast<int64_t>(blockIdx.x) * g.H + h) * state_stride;
-#pragma unroll
-  for (int k = 0; k < kMaxRows; ++k) {
-    const int Di = r + k * R;
-    if (k < nrows && Di < D) out[Di * (d + 1) + c] = acc[k];
-  }
-  if (tid < D) out[tid * (d + 1) + d] = zacc;
-}
-
-// Sum the partial states of each (sequence, head) in chunk order (deterministic).
-// grid (num_seqs, H), block 256.
-__global__ void k_reduce(Geom g, const int32_t* __restrict__ seq_chunk_off,
-                         const float* __restrict__ partial, float* __restrict__ state,
-                         int64_t state_stride, int count) {
-  const int s = blockIdx.x, h = blockIdx.y;
-  const int c0 = seq_chunk_off[s], c1 = seq_chunk_off[s + 1];
-  float* out = state + (static_cast<int64_t>(s) * g.H + h) * state_stride;
-  for (int i = threadIdx.x; i < count; i += blockDim.x) {
-    float a = 0.0f;
-    for (int ch = c0; ch < c1; ++ch) a += partial[(static_cast<int64_t>(ch) * g.H + h) * state_stride + i];
-    out[i] = a;
-  }
-}
-
-// ---- contract: out_i = T_i . M -----------------------------------------------------------------
-// QUERY = true : T = T_q, M = Chat; writes O = num / (eta + eps) and den = eta + eps
-// QUERY = false: T = T_k, M = dChat; writes dV = first d columns
-// grid (tiles, H), block 256; tile = kTokPerThread * R tokens; thread (r, c) owns column c of
-// tokens r + k*R.
-template <typename T, bool QUERY>
-__global__ void k_contract(Geom g, const BlockEnt* __restrict__ tiles,
-                           const float* __restrict__ feat, const float* __restrict__ M,
-                           int64_t state_stride, View Out, float* __restrict__ den) {
-  extern __shared__ float smem[];
-  const int d = g.d, D = g.D;
-  const int R = kThreads / d;
-  const int tile = kTokPerThread * R;
-  float* ts = smem;             // [tile][D]
-  float* fs = ts + tile * D;    // [tile][nfeat]
-  float* etas = fs + tile * g.nfeat;  // [tile]
-  const BlockEnt e = tiles[blockIdx.x];
-  const int h = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int c = tid % d, r = tid / d;
-  const int nt = e.t1 - e.t0;
-  const float* Mu = M + (static_cast<int64_t>(e.seq) * g.H + h) * state_stride;
-  for (int idx = tid; idx < tile * g.nfeat; idx += kThreads) {
-    const int t = idx / g.nfeat;
-    fs[idx] = t < nt ? feat[g.th(e.b, h, e.t0 + t) * g.nfeat + idx % g.nfeat] : 0.0f;
-  }
-  __syncthreads();
-  for (int idx = tid; idx < tile * D; idx += kThreads) {
-    const int t = idx / D, Di = idx % D;
-    ts[idx] = outer_entry(fs + t * g.nfeat, QUERY, Di, g.F, g.dphi);
-  }
-  __syncthreads();
-  float acc[kTokPerThread];
-#pragma unroll
-  for (int k = 0; k < kTokPerThread; ++k) acc[k] = 0.0f;
-  for (int Di = 0; Di < D; ++Di) {
-    const float mv = Mu[Di * (d + 1) + c];
-#pragma unroll
-    for (int k = 0; k < kTokPerThread; ++k) acc[k] += ts[(k * R + r) * D + Di] * mv;
-  }
-  if (QUERY) {
-    if (tid < tile) {
-      float eta = 0.0f;
-      for (int Di = 0; Di < D; ++Di) eta += ts[tid * D + Di] * Mu[Di * (d + 1) + d];
-      etas[tid] = eta + g.eps;
-      if (tid < nt) den[g.th(e.b, h, e.t0 + tid)] = eta + g.eps;
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 0; k < kTokPerThread; ++k) {
-    const int t = k * R + r;
-    if (t < nt) {
-      const float o = QUERY ? acc[k] / etas[t] : acc[k];
-      Out.row<T>(e.b, h, e.t0 + t)[c] = from_float<T>(o);
-    }
-  }
-}
-
 // ghat_i = [dO_i / den_i | -<dO_i, o_i> / den_i]   (one block row of d threads per token)
 // grid (ceil(N/R), H, B), block 256.
 template <typename T>
@@ -647,58 +499,6 @@ __device__ __forceinline__ void slot_gradients(const Geom& g, const float* fs, c
     const int col = QUERY ? a : (1 + s_lo) * dphi + a;
     dfeat[g.fidx(g.th(b, h, t0 + t), col)] = grad;
   }
-}
-
-// ---- dtensor: dT_i = M yhat_i, then gradients of the outer-product slots -----------------------
-// QUERY = true : M = Chat, yhat = ghat (dense scratch), slots all phi_q -> dfeat[.., 0:dphi] (summed)
-// QUERY = false: M = dChat, yhat = [V | 1] (caller's V), slot f -> dfeat[.., (1+f)*dphi : ..]
-// grid (tiles of kDtTile, H), block 256 (needs D <= 256).
-template <typename T, bool QUERY>
-__global__ void k_dtensor(Geom g, const BlockEnt* __restrict__ tiles,
-                          const float* __restrict__ feat, const float* __restrict__ M,
-                          int64_t state_stride, View Y, const float* __restrict__ ydense,
-                          float* __restrict__ dfeat) {
-  extern __shared__ float smem[];
-  const int d = g.d, D = g.D;
-  float* ys = smem;                       // [kDtTile][d+1]
-  float* fs = ys + kDtTile * (d + 1);     // [kDtTile][nfeat]
-  float* dts = fs + kDtTile * g.nfeat;    // [kDtTile][D]
-  const BlockEnt e = tiles[blockIdx.x];
-  const int h = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int nt = e.t1 - e.t0;
-  const float* Mu = M + (static_cast<int64_t>(e.seq) * g.H + h) * state_stride;
-  for (int idx = tid; idx < kDtTile * g.nfeat; idx += kThreads) {
-    const int t = idx / g.nfeat;
-    fs[idx] = t < nt ? feat[g.th(e.b, h, e.t0 + t) * g.nfeat + idx % g.nfeat] : 0.0f;
-  }
-  for (int idx = tid; idx < kDtTile * (d + 1); idx += kThreads) {
-    const int t = idx / (d + 1), cc = idx % (d + 1);
-    float y = 0.0f;
-    if (t < nt) {
-      if (QUERY)
-        y = ydense[g.th(e.b, h, e.t0 + t) * (d + 1) + cc];
-      else
-        y = cc < d ? to_float(Y.row<const T>(e.b, h, e.t0 + t)[cc]) : 1.0f;
-    }
-    ys[idx] = y;
-  }
-  __syncthreads();
-  if (tid < D) {
-    float dt[kDtTile];
-#pragma unroll
-    for (int t = 0; t < kDtTile; ++t) dt[t] = 0.0f;
-    const float* mrow = Mu + tid * (d + 1);
-    for (int cc = 0; cc <= d; ++cc) {
-      const float mv = mrow[cc];
-#pragma unroll
-      for (int t = 0; t < kDtTile; ++t) dt[t] += mv * ys[t * (d + 1) + cc];
-    }
-#pragma unroll
-    for (int t = 0; t < kDtTile; ++t) dts[t * D + tid] = dt[t];
-  }
-  __syncthreads();
-  slot_gradients<QUERY>(g, fs, dts, kDtTile, nt, e.b, h, e.t0, dfeat);
 }
 
 // ---- causal variant (Sec. 4.4): one scan over the tokens of a (sequence, head) ------------------
@@ -934,70 +734,15 @@ hla_status causal_scan(hla_handle* hd, const hla_call_args& a, const char* name,
 }
 
 template <typename T>
-hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
-  Geom g = hd->g;
-  hipStream_t s = a.stream;
-  const int d = g.d;
-  const int R = kThreads / d;
-  HLA_TRY(features_in_t<T>(hd, a));
-  if (hd->cfg.causal) return causal_scan<T, 0>(hd, a, "generic_causal_forward", a.O);
-  hla_token_table *chunks = nullptr, *tiles = nullptr;
-  HLA_TRY(get_table(hd, 0, kChunk, s, &chunks));
-  HLA_TRY(get_table(hd, 1, kTokPerThread * R, s, &tiles));
-  const int nrows = (g.D + R - 1) / R;
-  const size_t sh_acc = (kAccTile * nrows * R + kAccTile * (d + 1) + kAccTile * g.nfeat) * sizeof(float);
-  HLA_TRY(launch(hd, "generic_state_accumulate", k_accumulate<T, true>, dim3(chunks->count, g.H),
-                 dim3(kThreads), sh_acc, s, g, chunks->dev, hd->feat, false, a.V,
-                 static_cast<const float*>(nullptr), hd->partial, hd->state_stride));
-  HLA_TRY(launch(hd, "generic_state_reduce", k_reduce, dim3(a.num_seqs, g.H), dim3(256), 0, s, g,
-                 chunks->seq_off_dev, hd->partial, hd->state, hd->state_stride, g.D * (d + 1)));
-  const int tile = kTokPerThread * R;
-  const size_t sh_c = (static_cast<size_t>(tile) * g.D + tile * g.nfeat + tile) * sizeof(float);
-  HLA_TRY(launch(hd, "generic_query_contract", k_contract<T, true>, dim3(tiles->count, g.H),
-                 dim3(kThreads), sh_c, s, g, tiles->dev, hd->feat, hd->state, hd->state_stride, a.O,
-                 hd->den));
-  return HLA_OK;
-}
-
-template <typename T>
-hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
-  Geom g = hd->g;
-  hipStream_t s = a.stream;
-  const int d = g.d;
-  const int R = kThreads / d;
-  hla_token_table *chunks = nullptr, *tiles = nullptr, *dtt = nullptr;
-  HLA_TRY(get_table(hd, 0, kChunk, s, &chunks));
-  HLA_TRY(get_table(hd, 1, kTokPerThread * R, s, &tiles));
-  HLA_TRY(get_table(hd, 2, kDtTile, s, &dtt));
+hla_status causal_backward_t(hla_handle* hd, const hla_call_args& a) {
+  const Geom& g = hd->g;
+  const int R = kThreads / g.d;
   HLA_TRY(launch(hd, "generic_backward_prep", k_backward_prep<T>, dim3((g.N + R - 1) / R, g.H, g.B),
-                 dim3(kThreads), 0, s, g, a.dO, a.O, hd->den, hd->yhat));
-  if (hd->cfg.causal) {
-    // the same state recurrence once more for d(phi_q), its mirror image from the back for
-    // d(phi_k) and dV
-    HLA_TRY((causal_scan<T, 1>(hd, a, "generic_causal_dquery", a.dV)));
-    HLA_TRY((causal_scan<T, 2>(hd, a, "generic_causal_dkey", a.dV)));
-    return features_out_t<T>(hd, a);
-  }
-  const int nrows = (g.D + R - 1) / R;
-  const size_t sh_acc = (kAccTile * nrows * R + kAccTile * (d + 1) + kAccTile * g.nfeat) * sizeof(float);
-  HLA_TRY(launch(hd, "generic_dstate_accumulate", k_accumulate<T, false>, dim3(chunks->count, g.H),
-                 dim3(kThreads), sh_acc, s, g, chunks->dev, hd->feat, true, a.V, hd->yhat, hd->partial,
-                 hd->state_stride));
-  HLA_TRY(launch(hd, "generic_dstate_reduce", k_reduce, dim3(a.num_seqs, g.H), dim3(256), 0, s, g,
-                 chunks->seq_off_dev, hd->partial, hd->dstate, hd->state_stride, g.D * (d + 1)));
-  const size_t sh_dt = (kDtTile * (d + 1) + kDtTile * g.nfeat + static_cast<size_t>(kDtTile) * g.D) * sizeof(float);
-  HLA_TRY(launch(hd, "generic_dquery_features", k_dtensor<T, true>, dim3(dtt->count, g.H),
-                 dim3(kThreads), sh_dt, s, g, dtt->dev, hd->feat, hd->state, hd->state_stride, a.V,
-                 hd->yhat, hd->dfeat));
-  HLA_TRY(launch(hd, "generic_dkey_features", k_dtensor<T, false>, dim3(dtt->count, g.H),
-                 dim3(kThreads), sh_dt, s, g, dtt->dev, hd->feat, hd->dstate, hd->state_stride, a.V,
-                 static_cast<const float*>(nullptr), hd->dfeat));
-  const int tile = kTokPerThread * R;
-  const size_t sh_c = (static_cast<size_t>(tile) * g.D + tile * g.nfeat + tile) * sizeof(float);
-  HLA_TRY(launch(hd, "generic_dvalue_contract", k_contract<T, false>, dim3(tiles->count, g.H),
-                 dim3(kThreads), sh_c, s, g, tiles->dev, hd->feat, hd->dstate, hd->state_stride, a.dV,
-                 static_cast<float*>(nullptr)));
-  return features_out_t<T>(hd, a);
+                 dim3(kThreads), 0, a.stream, g, a.dO, a.O, hd->den, hd->yhat));
+  // the same state recurrence once more for d(phi_q), its mirror image from the back for
+  // d(phi_k) and dV
+  HLA_TRY((causal_scan<T, 1>(hd, a, "generic_causal_dquery", a.dV)));
+  return causal_scan<T, 2>(hd, a, "generic_causal_dkey", a.dV);
 }
 
 }  // namespace
@@ -1005,26 +750,21 @@ hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
 hla_status generic_workspace_plan(hla_handle* hd) {
   const Geom& g = hd->g;
   if (g.F > kMaxF || g.D > kThreads) return HLA_ERR_UNSUPPORTED;
-  const int R = kThreads / g.d;
-  if ((g.D + R - 1) / R > kMaxRows) return HLA_ERR_UNSUPPORTED;
   if (kPhiTile * g.dphi > 64 * 1024) return HLA_ERR_UNSUPPORTED;
-  hd->state_stride = static_cast<int64_t>(g.D) * (g.d + 1);
-  hd->max_chunks = (hd->cfg.max_tokens + kChunk - 1) / kChunk + hd->cfg.max_seqs;
+  if (!hd->cfg.causal) return f32_workspace_plan(hd);
+  // the scan keeps its state in LDS: token table and the augmented gradient rows only
+  if (causal_scan_tile(g) == 0) return HLA_ERR_UNSUPPORTED;
+  hd->state_stride = 1;
+  hd->max_chunks = 1;
   hd->yhat_floats = hd->max_th * (g.d + 1);
   hd->tables[0].min_block = kChunk;
-  hd->tables[1].min_block = kTokPerThread * R;
-  hd->tables[2].min_block = kDtTile;
-  // shared-memory budgets (64 KiB static+dynamic without opting in)
-  const size_t tile = kTokPerThread * R;
-  const size_t sh_c = (tile * g.D + tile * g.nfeat + tile) * sizeof(float);
-  if (sh_c > 64 * 1024) return HLA_ERR_UNSUPPORTED;
-  if (hd->cfg.causal && causal_scan_tile(g) == 0) return HLA_ERR_UNSUPPORTED;  // the scan's state does not fit LDS
   return HLA_OK;
 }
 
-// Kernel attributes a handle on this path needs (once per handle, at creation).
-hla_status generic_prepare_kernels(const hla_handle* hd) {
-  if (!hd->cfg.causal) return HLA_OK;
+// What a handle on this path needs once: kernel attributes and, where the form has none at compile
+// time, the monomial tables (written on `s`).
+hla_status generic_prepare_kernels(const hla_handle* hd, hipStream_t s) {
+  if (!hd->cfg.causal) return f32_prepare_kernels(hd, s);
   const Geom& g = hd->g;
   const bool f32 = hd->cfg.io_dtype == HLA_F32;
   switch (causal_scan_tile(g)) {
@@ -1105,11 +845,18 @@ hla_status generic_features_out(hla_handle* hd, const hla_call_args& a) {
 }
 
 hla_status generic_forward(hla_handle* hd, const hla_call_args& a) {
-  return hd->cfg.io_dtype == HLA_F32 ? forward_t<float>(hd, a) : forward_t<bf16_t>(hd, a);
+  HLA_TRY(generic_features_in(hd, a));
+  if (!hd->cfg.causal) return f32_forward(hd, a);
+  return hd->cfg.io_dtype == HLA_F32 ? causal_scan<float, 0>(hd, a, "generic_causal_forward", a.O)
+                                     : causal_scan<bf16_t, 0>(hd, a, "generic_causal_forward", a.O);
 }
 
 hla_status generic_backward(hla_handle* hd, const hla_call_args& a) {
-  return hd->cfg.io_dtype == HLA_F32 ? backward_t<float>(hd, a) : backward_t<bf16_t>(hd, a);
+  if (!hd->cfg.causal)
+    HLA_TRY(f32_backward(hd, a));
+  else
+    HLA_TRY(hd->cfg.io_dtype == HLA_F32 ? causal_backward_t<float>(hd, a) : causal_backward_t<bf16_t>(hd, a));
+  return generic_features_out(hd, a);
 }
 
 }  // namespace hla

@@ -1,0 +1,66 @@
+"""The fp32 matrix-core kernels of the generic path at the edges of their tiles: token counts around
+the 64-token (paper's forms) and 32-token (run-time form) tile and around a run of several tiles, forms
+with an odd number of monomials, the largest form, and views whose rows cannot be read 16 bytes at a
+time, against the CPU oracle.  The bound is the path's 1e-4 of max|ref| (fp32 sums: 1e-6 measured)."""
+import pytest
+import torch
+
+import paper_2602_12128_amd as hla
+from paper_2602_12128_amd import workloads as wl
+from tests import parity_utils as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("F,dphi,d,H,N,lens", [
+    (3, 6, 64, 1, 63, None),
+    (3, 6, 128, 3, 65, None),
+    (2, 12, 128, 2, 129, None),
+    (2, 12, 32, 1, 64, None),
+    (3, 6, 32, 5, 8200, None),         # more tiles than partial states: runs of several tiles
+    (3, 5, 64, 2, 33, None),           # 35 monomials: an odd row count
+    (1, 256, 32, 1, 31, None),         # 256 monomials of one factor
+    (2, 16, 128, 2, 97, None),         # 136 monomials
+    (4, 4, 128, 2, 1, None),
+    (3, 6, 128, 2, None, [1, 64, 0, 127, 300]),
+    (2, 3, 64, 2, None, [5, 0, 70]),
+])
+def test_tile_edges(F, dphi, d, H, N, lens):
+    cu = None
+    if lens is not None:
+        cu = [0]
+        for n in lens:
+            cu.append(cu[-1] + n)
+        N = cu[-1]
+    t = wl.make_feature_inputs(3000 + 7 * N + dphi, 1, H, N, d, F, dphi, torch.float32)
+    gpu = pu.run_gpu(t, F, dphi, 1e-6, cu_seqlens=cu, path=hla.HLA_PATH_GENERIC)
+    ref = pu.run_oracle(t, F, dphi, 1e-6, cu_seqlens=cu)
+    # one-token sequences: dQ, dK are what two cancelling terms leave behind
+    scale = None
+    if lens is not None and 1 in lens:
+        scale = pu.short_sequence_rows(t, ref, cu)
+    elif N == 1:
+        scale = pu.short_sequence_rows(t, ref, [0, 1])
+    pu.assert_parity(gpu, ref, 1e-4, f"f32 tiles F={F} dphi={dphi} d={d} N={N}", row_scale=scale)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_off_sixteen_bytes(dtype):
+    B, H, N, d, F, dphi = 1, 2, 150, 64, 3, 6
+    t = wl.make_feature_inputs(3100, B, H, N, d, F, dphi, dtype)
+    h = pu.make_handle(t, F, dphi, 1e-6, None, None, hla.HLA_PATH_GENERIC)
+
+    def shifted(x):  # the same values in rows of d + 3 elements, one element off the allocation's start
+        buf = torch.zeros(x.shape[:3] + (x.shape[3] + 3,), dtype=x.dtype, device="cuda")
+        v = buf[..., 1:1 + x.shape[3]]
+        v.copy_(x)
+        return v
+
+    td = {k: shifted(v) for k, v in t.items()}
+    out = {"O": shifted(t["V"]), "dQ": shifted(t["Q"]), "dK": shifted(t["K"]), "dV": shifted(t["V"])}
+    h.forward(td["Q"], td["K"], td["V"], out["O"])
+    h.backward(td["Q"], td["K"], td["V"], out["O"], td["dO"], out["dQ"], out["dK"], out["dV"])
+    torch.cuda.synchronize()
+    h.destroy()
+    ref = pu.run_oracle(t, F, dphi, 1e-6)
+    pu.assert_parity({k: v.contiguous().cpu() for k, v in out.items()}, ref, pu.TOL[dtype], "f32 rows off 16 bytes")
