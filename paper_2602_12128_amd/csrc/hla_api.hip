@@ -150,6 +150,7 @@ void free_all(hla_handle* hd) {
     (void)hipFree(hd->partial);
     (void)hipFree(hd->path_ws);
     (void)hipFree(hd->w_f32);
+    (void)hipFree(hd->w_f32_t);
     (void)hipFree(hd->wg_partial);
     (void)hipFree(hd->vmod_w);
     (void)hipFree(hd->vmod_wpk);
@@ -271,6 +272,8 @@ hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only) {
     const int64_t per_map = static_cast<int64_t>(c.head_dim) * c.head_dim + c.head_dim +
                             static_cast<int64_t>(c.head_dim) * c.feature_dim + c.feature_dim;
     HLA_TRY(arena.alloc(&hd->w_f32, per_map * (1 + c.degree) * c.max_heads));
+    if (hd->path == HLA_PATH_GENERIC)
+      HLA_TRY(arena.alloc(&hd->w_f32_t, static_cast<int64_t>(c.head_dim) * c.head_dim * (1 + c.degree) * c.max_heads));
   }
   for (hla_token_table& t : hd->tables) {
     if (t.min_block <= 0) continue;
@@ -376,6 +379,8 @@ hla_status hla_set_phi_weight_grads(hla_handle* hd, const hla_phi_weight_grads* 
     // (map, head)
     const int64_t groups = g.d >= 32 ? 8 * 32 / g.d : 8;
     hd->wg_parts_cap = 256 * (groups < 2 ? 2 : groups) + 2 * static_cast<int64_t>(num_maps) * hd->cfg.max_heads;
+    if (hd->path == HLA_PATH_GENERIC)
+      hd->wg_parts_cap = static_cast<int64_t>(num_maps) * std::max(f32_phi_parts(g.d), hd->cfg.max_heads);
     Arena arena;  // hipMalloc
     HLA_TRY(arena.alloc(&hd->wg_partial, hd->wg_parts_cap * hd->wg_part_floats));
   }

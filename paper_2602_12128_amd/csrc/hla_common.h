@@ -89,6 +89,7 @@ struct PhiF32 {
   const float* b1;
   const float* W2;
   const float* b2;
+  const float* W1T;  // [maps][heads_w][d (hidden)][d (input)], generic path only
   int32_t heads_w;
 };
 

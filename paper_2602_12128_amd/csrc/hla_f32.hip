@@ -14,26 +14,13 @@
 // that time, so plain LDS operands keep the pipe fed without register blocking.
 #include <algorithm>
 
-#include "hla_handle.h"
-#include "hla_mfma_common.h"
+#include "hla_f32_common.h"
 
 namespace hla {
 namespace {
 
-using mf::f32x16;
-using mf::f32x4;
+using namespace f32;
 using mf::static_for;
-
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
-  // A: lane l holds A[l % 32][l / 32]; B: B[l / 32][l % 32]; D as in the bf16 32x32 shapes
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-  return z;
-}
 
 // ---- forms --------------------------------------------------------------------------------------
 // The paper's two forms with everything about their monomials known at compile time, and the
@@ -71,31 +58,6 @@ struct F32Geom {
   int vec;          // bit i: rows of view i can be read and written 16 bytes at a time
   const MonoTable* tab;
 };
-
-// Rows [t0, t0 + nt) of a caller's tensor into LDS as fp32, row stride LD floats; rows from nt on are
-// zero.  16-byte loads where the view's pointer and strides allow it.
-template <int D, int TOK, int THREADS, int LD>
-__device__ __forceinline__ void stage_rows(const View& X, int b, int h, int t0, int nt, bool bf16, bool vec,
-                                           float* dst) {
-  if (vec && !bf16) {
-    constexpr int P = D / 4;  // float4 pieces per row
-#pragma unroll
-    for (int i = 0; i < TOK * P / THREADS; ++i) {
-      const int idx = threadIdx.x + i * THREADS, t = idx / P, p = idx % P;
-      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (t < nt) v = *reinterpret_cast<const f32x4*>(X.row<const float>(b, h, t0 + t) + 4 * p);
-      *reinterpret_cast<f32x4*>(dst + t * LD + 4 * p) = v;
-    }
-    return;
-  }
-#pragma unroll 4
-  for (int i = 0; i < TOK * D / THREADS; ++i) {
-    const int idx = threadIdx.x + i * THREADS, t = idx / D, c = idx % D;
-    float v = 0.0f;
-    if (t < nt) v = bf16 ? to_float(X.row<const bf16_t>(b, h, t0 + t)[c]) : X.row<const float>(b, h, t0 + t)[c];
-    dst[t * LD + c] = v;
-  }
-}
 
 // columns [off, off + n) of the feature rows of TOK consecutive token-heads, LDS row stride ld
 template <int TOK, int THREADS>
@@ -242,7 +204,7 @@ __device__ __forceinline__ void accumulate_state(int mpb, const float* mt, const
       for (int k4 = 0; k4 < TOK / 8; ++k4) {  // tokens (TOK / 2) hf + 4 k4 + 0..3
         const f32x4 a = *reinterpret_cast<const f32x4*>(ap + 4 * k4);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i] = mfma_f32(a[j], bp[(4 * k4 + j) * LD], acc[i]);
+        for (int j = 0; j < 4; ++j) acc[i] = mfma32(a[j], bp[(4 * k4 + j) * LD], acc[i]);
       }
     }
   }
@@ -268,7 +230,7 @@ __device__ __forceinline__ void rows_times_state(int mpb, const float* C, const 
         const f32x4 a = *reinterpret_cast<const f32x4*>(ap + 4 * k4);
         const f32x4 b = *reinterpret_cast<const f32x4*>(bp + 4 * k4);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = mfma_f32(a[j], b[j], acc);
+        for (int j = 0; j < 4; ++j) acc = mfma32(a[j], b[j], acc);
       }
 #pragma unroll
       for (int j = 0; j < 16; ++j) xt[(32 * mb + mf::d_row(j, hf)) * LT + 32 * tb + r] = acc[j];
@@ -295,12 +257,12 @@ __device__ __forceinline__ void monomials_times_state(const F32Geom& x, const fl
       if constexpr (!FM::kRt) {
         static_assert(FM::NM % 2 == 0, "whole k-steps");
 #pragma unroll 8
-        for (int s = 0; s < FM::NM / 2; ++s) acc = mfma_f32(ap[2 * s * LT], bp[2 * s * LC], acc);
+        for (int s = 0; s < FM::NM / 2; ++s) acc = mfma32(ap[2 * s * LT], bp[2 * s * LC], acc);
       } else {
         const int steps = (x.nm + 1) / 2;  // row nm of an odd form: zero in mt, masked in C
         for (int s = 0; s < steps; ++s) {
           const float bv = 2 * s + hf < x.nm ? bp[static_cast<int64_t>(2 * s) * LC] : 0.0f;
-          acc = mfma_f32(ap[2 * s * LT], bv, acc);
+          acc = mfma32(ap[2 * s * LT], bv, acc);
         }
       }
 #pragma unroll
@@ -759,11 +721,6 @@ F32Geom f32_geom(const hla_handle* hd) {
 bool is_form(const hla_handle* hd, int F, int dphi) { return hd->g.F == F && hd->g.dphi == dphi; }
 bool is_rt(const hla_handle* hd) { return !is_form(hd, 3, 6) && !is_form(hd, 2, 12); }
 int tok_of(const hla_handle* hd) { return is_rt(hd) ? FormRt::TOK : 64; }
-
-// 16-byte accesses need the pointer and every stride of the view on 16 bytes
-bool rows_vec(const View& v, size_t elem) {
-  return ((reinterpret_cast<uintptr_t>(v.ptr) | (v.sb * elem) | (v.sh * elem) | (v.sn * elem)) & 15) == 0;
-}
 
 // Runs of tokens per (sequence, head): enough workgroups for two per compute unit, never more
 // partial states than the workspace holds (but at least one run per sequence).

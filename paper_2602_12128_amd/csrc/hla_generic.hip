@@ -1,7 +1,7 @@
-// Generic path, common parts: feature import / export, the feature maps and their gradients on the
-// fp32 vector ALU, and the causal variant as a token-by-token scan over the literal d_phi^F feature
+// Generic path, common parts: feature import / export, conversion of the feature-map weights, the sum
+// of their gradients' partials, and the causal variant as a token-by-token scan over the literal d_phi^F feature
 // tensor (a cross-check of the matrix-core path; throughput is not a goal there).  The non-causal
-// operator of this path is hla_f32.hip.
+// operator of this path is hla_f32.hip, its feature maps hla_f32_phi.hip.
 //
 // The scan uses the augmented state  Chat = [C | z]  ([D, d+1]) and augmented per-token rows
 // vhat_j = [v_j | 1], ghat_i = [dO_i/den_i | -<dO_i,o_i>/den_i].
@@ -14,18 +14,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kChunk = 1024;      // tokens per table entry of the causal scan
-constexpr int kPhiTile = 16;      // feature maps: tokens per block
-constexpr int kWgTile = 8;        // weight gradients: tokens staged per step
 constexpr int kMaxF = 4;
-
-__device__ __forceinline__ float gelu_erf(float h) {
-  return h * 0.5f * (1.0f + erff(h * 0.70710678118654752440f));
-}
-__device__ __forceinline__ float gelu_erf_grad(float h) {
-  const float cdf = 0.5f * (1.0f + erff(h * 0.70710678118654752440f));
-  const float pdf = 0.39894228040143267794f * expf(-0.5f * h * h);
-  return cdf + h * pdf;
-}
 
 // Slot offsets into a feature row: query tensors use phi_q in every slot, key tensors use map f.
 __device__ __forceinline__ int slot_offset(bool query, int slot, int dphi) {
@@ -141,213 +130,7 @@ __global__ void k_dfeat_export(Geom g, const float* __restrict__ dfeat, View dQ,
   for (int j = g.dphi; j < g.nfeat; ++j) k[j - g.dphi] = from_float<T>(dfeat[g.fidx(th, j)]);
 }
 
-// ---- feature maps (App. A.1) ------------------------------------------------------------------
-// grid (ceil(N/kPhiTile), H, B), block d threads.  Thread j owns hidden unit j.
-template <typename T>
-__global__ void k_phi_forward(Geom g, PhiF32 w, View Q, View K, float* __restrict__ feat) {
-  extern __shared__ float smem[];
-  const int d = g.d, dphi = g.dphi;
-  float* xs = smem;                 // [kPhiTile][d]
-  float* gs = smem + kPhiTile * d;  // [kPhiTile][d]
-  const int j = threadIdx.x;
-  const int n0 = blockIdx.x * kPhiTile, h = blockIdx.y, b = blockIdx.z;
-  const int nt = min(kPhiTile, g.N - n0);
-  const int hw = w.heads_w == 1 ? 0 : h;
-  for (int m = 0; m <= g.F; ++m) {
-    if (m <= 1) {
-      __syncthreads();
-      const View& X = m == 0 ? Q : K;
-      for (int t = 0; t < kPhiTile; ++t)
-        xs[t * d + j] = t < nt ? to_float(X.row<const T>(b, h, n0 + t)[j]) : 0.0f;
-      __syncthreads();
-    }
-    const int64_t mh = static_cast<int64_t>(m) * w.heads_w + hw;
-    const float* W1 = w.W1 + mh * d * d;
-    const float* W2 = w.W2 + mh * d * dphi;
-    float acc[kPhiTile];
-#pragma unroll
-    for (int t = 0; t < kPhiTile; ++t) acc[t] = 0.0f;
-    for (int i = 0; i < d; ++i) {
-      const float wv = W1[i * d + j];
-#pragma unroll
-      for (int t = 0; t < kPhiTile; ++t) acc[t] += xs[t * d + i] * wv;
-    }
-    const float bias = w.b1[mh * d + j];
-#pragma unroll
-    for (int t = 0; t < kPhiTile; ++t) gs[t * d + j] = gelu_erf(acc[t] + bias);
-    __syncthreads();
-    for (int idx = j; idx < nt * dphi; idx += d) {
-      const int t = idx / dphi, c = idx % dphi;
-      float u = w.b2[mh * dphi + c];
-      for (int jj = 0; jj < d; ++jj) u += gs[t * d + jj] * W2[jj * dphi + c];
-      feat[g.fidx(g.th(b, h, n0 + t), m * dphi + c)] = fmaxf(u, 0.0f);
-    }
-    __syncthreads();
-  }
-}
-
-// Input gradients through the feature maps; hidden activations are recomputed.  dK sums the F
-// key maps.  Thread j owns hidden unit j and input coordinate j.
-template <typename T>
-__global__ void k_phi_backward(Geom g, PhiF32 w, View Q, View K, const float* __restrict__ feat,
-                               const float* __restrict__ dfeat, View dQ, View dK) {
-  extern __shared__ float smem[];
-  const int d = g.d, dphi = g.dphi;
-  float* xs = smem;                   // [kPhiTile][d]
-  float* dhs = xs + kPhiTile * d;     // [kPhiTile][d]
-  float* dus = dhs + kPhiTile * d;    // [kPhiTile][dphi]
-  const int j = threadIdx.x;
-  const int n0 = blockIdx.x * kPhiTile, h = blockIdx.y, b = blockIdx.z;
-  const int nt = min(kPhiTile, g.N - n0);
-  const int hw = w.heads_w == 1 ? 0 : h;
-  float dx[kPhiTile];
-  for (int m = 0; m <= g.F; ++m) {
-    if (m <= 1) {
-      __syncthreads();
-      const View& X = m == 0 ? Q : K;
-      for (int t = 0; t < kPhiTile; ++t)
-        xs[t * d + j] = t < nt ? to_float(X.row<const T>(b, h, n0 + t)[j]) : 0.0f;
-#pragma unroll
-      for (int t = 0; t < kPhiTile; ++t) dx[t] = 0.0f;
-    }
-    __syncthreads();
-    for (int idx = j; idx < kPhiTile * dphi; idx += d) {
-      const int t = idx / dphi, c = idx % dphi;
-      float du = 0.0f;
-      if (t < nt) {
-        const int64_t o = g.fidx(g.th(b, h, n0 + t), m * dphi + c);
-        du = feat[o] > 0.0f ? dfeat[o] : 0.0f;  // ReLU passes gradient only where it was open
-      }
-      dus[idx] = du;
-    }
-    __syncthreads();
-    const int64_t mh = static_cast<int64_t>(m) * w.heads_w + hw;
-    const float* W1 = w.W1 + mh * d * d;
-    const float* W2 = w.W2 + mh * d * dphi;
-    float acc[kPhiTile];
-#pragma unroll
-    for (int t = 0; t < kPhiTile; ++t) acc[t] = 0.0f;
-    for (int i = 0; i < d; ++i) {
-      const float wv = W1[i * d + j];
-#pragma unroll
-      for (int t = 0; t < kPhiTile; ++t) acc[t] += xs[t * d + i] * wv;
-    }
-    const float bias = w.b1[mh * d + j];
-#pragma unroll
-    for (int t = 0; t < kPhiTile; ++t) {
-      float dg = 0.0f;
-      for (int c = 0; c < dphi; ++c) dg += dus[t * dphi + c] * W2[j * dphi + c];
-      dhs[t * d + j] = dg * gelu_erf_grad(acc[t] + bias);
-    }
-    __syncthreads();
-    for (int jj = 0; jj < d; ++jj) {
-      const float wv = W1[j * d + jj];  // dx_j = sum_jj dh_jj W1[j][jj]
-#pragma unroll
-      for (int t = 0; t < kPhiTile; ++t) dx[t] += dhs[t * d + jj] * wv;
-    }
-    if (m == 0 || m == g.F) {
-      const View& dX = m == 0 ? dQ : dK;
-      for (int t = 0; t < nt; ++t) dX.row<T>(b, h, n0 + t)[j] = from_float<T>(dx[t]);
-    }
-  }
-}
-
-// ---- weight gradients of the feature maps -----------------------------------------------------
-// dW1 = x^T dh, db1 = sum dh, dW2 = GELU(h)^T du, db2 = sum du over the tokens of a chunk; hidden
-// activations are recomputed.  grid (chunks, 1+F, heads_w), block DD = d threads.  Thread j owns
-// hidden unit j: column j of dW1, row j of dW2 and entry j of db1 stay in its registers for the
-// whole chunk, so nothing is reduced across threads.  The chunk's sums go to
-// partial[((map * gridDim.z + hw) * chunks + chunk)][d*d | d | d*dphi | dphi].
-// Token tiles: with shared weights (heads_w == 1) the tiles of all (batch row, head) pairs form
-// one list; with per-head weights the list of head blockIdx.z holds that head's tiles only.
-template <typename T, int DD>
-__global__ __launch_bounds__(DD) void k_phi_wgrad(Geom g, PhiF32 w, View Q, View K,
-                                                  const float* __restrict__ feat,
-                                                  const float* __restrict__ dfeat,
-                                                  float* __restrict__ partial) {
-  __shared__ float xs[kWgTile][DD];
-  __shared__ float dhs[kWgTile][DD];
-  __shared__ float dus[kWgTile][16];
-  const int dphi = g.dphi;
-  const int j = threadIdx.x;
-  const int chunk = blockIdx.x, nchunk = gridDim.x, m = blockIdx.y, hw = blockIdx.z;
-  const bool shared = w.heads_w == 1;
-  const int tpr = (g.N + kWgTile - 1) / kWgTile;
-  const int rows = shared ? g.B * g.H : g.B;
-  const int total = rows * tpr;
-  const int per = (total + nchunk - 1) / nchunk;
-  const int t_begin = chunk * per, t_end = min(total, t_begin + per);
-  const int64_t mh = static_cast<int64_t>(m) * w.heads_w + hw;
-  const float* W1 = w.W1 + mh * DD * DD;
-  const float* W2 = w.W2 + mh * DD * dphi;
-  const float bias = w.b1[mh * DD + j];
-  float w2row[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) w2row[c] = c < dphi ? W2[j * dphi + c] : 0.0f;
-  const View& X = m == 0 ? Q : K;
-  float dW1c[DD];     // column j of dW1
-  float dW2r[16];     // row j of dW2
-  float db1 = 0.0f, db2 = 0.0f;
-#pragma unroll
-  for (int i = 0; i < DD; ++i) dW1c[i] = 0.0f;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) dW2r[c] = 0.0f;
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    const int row = tile / tpr, n0 = (tile % tpr) * kWgTile;
-    const int b = shared ? row / g.H : row, h = shared ? row % g.H : hw;
-    const int nt = min(kWgTile, g.N - n0);
-    __syncthreads();
-    for (int t = 0; t < kWgTile; ++t) xs[t][j] = t < nt ? to_float(X.row<const T>(b, h, n0 + t)[j]) : 0.0f;
-    for (int idx = j; idx < kWgTile * 16; idx += DD) {
-      const int t = idx / 16, c = idx % 16;
-      float du = 0.0f;
-      if (t < nt && c < dphi) {
-        const int64_t o = g.fidx(g.th(b, h, n0 + t), m * dphi + c);
-        du = feat[o] > 0.0f ? dfeat[o] : 0.0f;  // ReLU passes gradient only where it was open
-      }
-      dus[t][c] = du;
-    }
-    __syncthreads();
-    float acc[kWgTile];
-#pragma unroll
-    for (int t = 0; t < kWgTile; ++t) acc[t] = bias;
-    for (int i = 0; i < DD; ++i) {
-      const float wv = W1[i * DD + j];
-#pragma unroll
-      for (int t = 0; t < kWgTile; ++t) acc[t] += xs[t][i] * wv;
-    }
-#pragma unroll
-    for (int t = 0; t < kWgTile; ++t) {
-      float dg = 0.0f;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) dg += dus[t][c] * w2row[c];
-      const float gv = gelu_erf(acc[t]);
-      const float dh = dg * gelu_erf_grad(acc[t]);
-      db1 += dh;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) dW2r[c] += gv * dus[t][c];
-      if (j < dphi) db2 += dus[t][j];
-      dhs[t][j] = dh;  // read back by this thread only
-    }
-    // one token at a time, so that only one row of x is in flight beside the DD accumulators
-#pragma unroll 1
-    for (int t = 0; t < kWgTile; ++t) {
-      const float dh = dhs[t][j];
-#pragma unroll
-      for (int i = 0; i < DD; ++i) dW1c[i] += xs[t][i] * dh;
-    }
-  }
-  float* out = partial + ((static_cast<int64_t>(m) * gridDim.z + hw) * nchunk + chunk) *
-                             (static_cast<int64_t>(DD) * DD + DD + DD * dphi + dphi);
-#pragma unroll
-  for (int i = 0; i < DD; ++i) out[i * DD + j] = dW1c[i];
-  out[DD * DD + j] = db1;
-#pragma unroll
-  for (int c = 0; c < 16; ++c)
-    if (c < dphi) out[DD * DD + DD + j * dphi + c] = dW2r[c];
-  if (j < dphi) out[DD * DD + DD + DD * dphi + j] = db2;
-}
-
+// ---- weight gradients of the feature maps: sum of the partials --------------------------------
 // Sum of the partial weight gradients of one (map, head) in partial order, times the scale of
 // its section, into the caller's arrays.  grid (ceil(floats / 256), 1+F, heads), block 256.
 struct WgradOut {
@@ -384,43 +167,6 @@ __global__ void k_wgrad_reduce(int d, int dphi, int nparts,
   } else {
     out.db2[m][static_cast<int64_t>(hw) * nb2 + (e - nW1 - nb1 - nW2)] = sb2 * sum;
   }
-}
-
-template <typename T>
-hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
-  Geom g = hd->g;
-  g.B = a.B;
-  g.H = a.H;
-  g.N = a.N;
-  if (g.dphi > 16) return HLA_ERR_UNSUPPORTED;
-  const int nm = 1 + g.F;
-  const int heads = hd->phi.heads_w == 1 ? 1 : a.H;
-  // about one full grid of workgroups in total, never more partial sums than the workspace holds
-  int64_t nchunk = 512 / (static_cast<int64_t>(nm) * heads);
-  const int64_t tiles = (hd->phi.heads_w == 1 ? static_cast<int64_t>(a.B) * a.H : a.B) *
-                        ((a.N + kWgTile - 1) / kWgTile);
-  if (nchunk > tiles) nchunk = tiles;
-  if (nchunk < 1) nchunk = 1;
-  if (nm * static_cast<int64_t>(heads) * nchunk > hd->wg_parts_cap) return HLA_ERR_STATE;
-  const dim3 grid(static_cast<unsigned>(nchunk), nm, heads);
-  hipStream_t s = a.stream;
-  switch (g.d) {
-    case 32:
-      HLA_TRY(launch(hd, "phi_weight_grads", k_phi_wgrad<T, 32>, grid, dim3(32), 0, s, g, hd->phi, a.Q, a.K,
-                     static_cast<const float*>(hd->feat), static_cast<const float*>(hd->dfeat), hd->wg_partial));
-      break;
-    case 64:
-      HLA_TRY(launch(hd, "phi_weight_grads", k_phi_wgrad<T, 64>, grid, dim3(64), 0, s, g, hd->phi, a.Q, a.K,
-                     static_cast<const float*>(hd->feat), static_cast<const float*>(hd->dfeat), hd->wg_partial));
-      break;
-    case 128:
-      HLA_TRY(launch(hd, "phi_weight_grads", k_phi_wgrad<T, 128>, grid, dim3(128), 0, s, g, hd->phi, a.Q, a.K,
-                     static_cast<const float*>(hd->feat), static_cast<const float*>(hd->dfeat), hd->wg_partial));
-      break;
-    default:
-      return HLA_ERR_UNSUPPORTED;
-  }
-  return weight_grads_reduce(hd, static_cast<int>(nchunk), heads, 1.0f, 1.0f, 1.0f, 1.0f, s);
 }
 
 // ghat_i = [dO_i / den_i | -<dO_i, o_i> / den_i]   (one block row of d threads per token)
@@ -659,35 +405,16 @@ __global__ __launch_bounds__(kThreads) void k_causal_scan(
 }
 
 template <typename T>
-hla_status features_in_t(hla_handle* hd, const hla_call_args& a) {
-  Geom g = hd->g;
-  hipStream_t s = a.stream;
-  const int d = g.d;
-  if (hd->cfg.phi_mode == HLA_PHI_NONE) {
-    const int64_t total = static_cast<int64_t>(g.B) * g.H * g.N;
-    return launch(hd, "generic_feat_import", k_feat_import<T>, dim3((total + 255) / 256), dim3(256),
-                  0, s, g, a.Q, a.K, hd->feat);
-  }
-  const size_t sh = 2 * kPhiTile * d * sizeof(float);
-  return launch(hd, "generic_phi_forward", k_phi_forward<T>,
-                dim3((g.N + kPhiTile - 1) / kPhiTile, g.H, g.B), dim3(d), sh, s, g, hd->phi, a.Q, a.K,
-                hd->feat);
+hla_status features_import_t(hla_handle* hd, const hla_call_args& a) {
+  const int64_t total = static_cast<int64_t>(hd->g.B) * hd->g.H * hd->g.N;
+  return launch(hd, "generic_feat_import", k_feat_import<T>, dim3((total + 255) / 256), dim3(256), 0, a.stream, hd->g,
+                a.Q, a.K, hd->feat);
 }
-
 template <typename T>
-hla_status features_out_t(hla_handle* hd, const hla_call_args& a) {
-  Geom g = hd->g;
-  hipStream_t s = a.stream;
-  const int d = g.d;
-  if (hd->cfg.phi_mode == HLA_PHI_NONE) {
-    const int64_t total = static_cast<int64_t>(g.B) * g.H * g.N;
-    return launch(hd, "generic_dfeat_export", k_dfeat_export<T>, dim3((total + 255) / 256), dim3(256),
-                  0, s, g, hd->dfeat, a.dQ, a.dK);
-  }
-  const size_t sh = (2 * kPhiTile * d + kPhiTile * g.dphi) * sizeof(float);
-  return launch(hd, "generic_phi_backward", k_phi_backward<T>,
-                dim3((g.N + kPhiTile - 1) / kPhiTile, g.H, g.B), dim3(d), sh, s, g, hd->phi, a.Q, a.K,
-                hd->feat, hd->dfeat, a.dQ, a.dK);
+hla_status features_export_t(hla_handle* hd, const hla_call_args& a) {
+  const int64_t total = static_cast<int64_t>(hd->g.B) * hd->g.H * hd->g.N;
+  return launch(hd, "generic_dfeat_export", k_dfeat_export<T>, dim3((total + 255) / 256), dim3(256), 0, a.stream,
+                hd->g, hd->dfeat, a.dQ, a.dK);
 }
 
 // The causal scan in one of its three modes; TT = 8 tokens per step where the LDS allows, else 4.
@@ -750,7 +477,6 @@ hla_status causal_backward_t(hla_handle* hd, const hla_call_args& a) {
 hla_status generic_workspace_plan(hla_handle* hd) {
   const Geom& g = hd->g;
   if (g.F > kMaxF || g.D > kThreads) return HLA_ERR_UNSUPPORTED;
-  if (kPhiTile * g.dphi > 64 * 1024) return HLA_ERR_UNSUPPORTED;
   if (!hd->cfg.causal) return f32_workspace_plan(hd);
   // the scan keeps its state in LDS: token table and the augmented gradient rows only
   if (causal_scan_tile(g) == 0) return HLA_ERR_UNSUPPORTED;
@@ -764,6 +490,7 @@ hla_status generic_workspace_plan(hla_handle* hd) {
 // What a handle on this path needs once: kernel attributes and, where the form has none at compile
 // time, the monomial tables (written on `s`).
 hla_status generic_prepare_kernels(const hla_handle* hd, hipStream_t s) {
+  if (hd->cfg.phi_mode == HLA_PHI_MLP) HLA_TRY(f32_phi_prepare_kernels(hd));
   if (!hd->cfg.causal) return f32_prepare_kernels(hd, s);
   const Geom& g = hd->g;
   const bool f32 = hd->cfg.io_dtype == HLA_F32;
@@ -788,7 +515,7 @@ hla_status convert_weights_to_f32(hla_handle* hd, const hla_phi_weights* maps, h
   float* b1 = W1 + nm * hw * nW1;
   float* W2 = b1 + nm * hw * nb1;
   float* b2 = W2 + nm * hw * nW2;
-  hd->phi = PhiF32{W1, b1, W2, b2, hw};
+  hd->phi = PhiF32{W1, b1, W2, b2, hd->w_f32_t, hw};
   for (int m = 0; m < nm; ++m) {
     struct Item {
       const void* src;
@@ -812,7 +539,7 @@ hla_status convert_weights_to_f32(hla_handle* hd, const hla_phi_weights* maps, h
   return HLA_OK;
 }
 
-hla_status generic_set_weights(hla_handle*, hipStream_t) { return HLA_OK; }
+hla_status generic_set_weights(hla_handle* hd, hipStream_t s) { return f32_phi_set_weights(hd, s); }
 
 hla_status weight_grads_reduce(hla_handle* hd, int nparts, int heads, float sW1, float sb1, float sW2,
                                float sb2, hipStream_t s) {
@@ -831,17 +558,19 @@ hla_status weight_grads_reduce(hla_handle* hd, int nparts, int heads, float sW1,
 }
 
 hla_status phi_weight_grads(hla_handle* hd, const hla_call_args& a) {
-  if (hd->path == HLA_PATH_MFMA && hd->cfg.io_dtype == HLA_BF16) return mfma_phi_weight_grads(hd, a);
-  return hd->cfg.io_dtype == HLA_F32 ? weight_grads_t<float>(hd, a) : weight_grads_t<bf16_t>(hd, a);
+  // the generic path's backward through the maps forms them along with the input gradients
+  return hd->path == HLA_PATH_MFMA ? mfma_phi_weight_grads(hd, a) : HLA_OK;
 }
 
 // Features in (feature maps, or import of caller-provided features) and feature gradients out
-// (through the maps, or exported as they are); shared with the MFMA path.
+// (through the maps, or exported as they are).  Import and export are shared with the MFMA path.
 hla_status generic_features_in(hla_handle* hd, const hla_call_args& a) {
-  return hd->cfg.io_dtype == HLA_F32 ? features_in_t<float>(hd, a) : features_in_t<bf16_t>(hd, a);
+  if (hd->cfg.phi_mode == HLA_PHI_MLP) return f32_phi_forward(hd, a);
+  return hd->cfg.io_dtype == HLA_F32 ? features_import_t<float>(hd, a) : features_import_t<bf16_t>(hd, a);
 }
 hla_status generic_features_out(hla_handle* hd, const hla_call_args& a) {
-  return hd->cfg.io_dtype == HLA_F32 ? features_out_t<float>(hd, a) : features_out_t<bf16_t>(hd, a);
+  if (hd->cfg.phi_mode == HLA_PHI_MLP) return f32_phi_backward(hd, a);
+  return hd->cfg.io_dtype == HLA_F32 ? features_export_t<float>(hd, a) : features_export_t<bf16_t>(hd, a);
 }
 
 hla_status generic_forward(hla_handle* hd, const hla_call_args& a) {

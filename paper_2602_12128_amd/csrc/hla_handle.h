@@ -58,6 +58,7 @@ struct hla_handle {
 
   // feature-map weights, fp32 copies (both paths keep them; the MFMA path adds packed bf16)
   float* w_f32 = nullptr;
+  float* w_f32_t = nullptr;        // W1 of every (map, head) transposed (generic path)
   hla::PhiF32 phi{};
   bool have_weights = false;
 
@@ -135,6 +136,13 @@ hla_status generic_prepare_kernels(const hla_handle* hd, hipStream_t s);
 // Non-causal operator of the generic path (hla_f32.hip).
 hla_status f32_workspace_plan(hla_handle* hd);
 hla_status f32_prepare_kernels(const hla_handle* hd, hipStream_t s);
+// Feature maps of the generic path and their gradients (hla_f32_phi.hip).  f32_phi_parts: most partial
+// weight gradients of a map; two workgroups per compute unit at d <= 64, one at d = 128.
+inline int f32_phi_parts(int d) { return d == 128 ? 256 : 512; }
+hla_status f32_phi_prepare_kernels(const hla_handle* hd);
+hla_status f32_phi_set_weights(hla_handle* hd, hipStream_t s);
+hla_status f32_phi_forward(hla_handle* hd, const hla_call_args& a);
+hla_status f32_phi_backward(hla_handle* hd, const hla_call_args& a);
 hla_status f32_forward(hla_handle* hd, const hla_call_args& a);
 hla_status f32_backward(hla_handle* hd, const hla_call_args& a);
 hla_status mfma_phi_prepare_kernels(const hla_handle* hd);

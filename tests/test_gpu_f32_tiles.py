@@ -64,3 +64,23 @@ def test_rows_off_sixteen_bytes(dtype):
     h.destroy()
     ref = pu.run_oracle(t, F, dphi, 1e-6)
     pu.assert_parity({k: v.contiguous().cpu() for k, v in out.items()}, ref, pu.TOL[dtype], "f32 rows off 16 bytes")
+
+
+@pytest.mark.parametrize("F,dphi,d,B,H,N", [
+    (4, 3, 128, 1, 1, 63),     # four key maps: the most accumulators a workgroup holds
+    (1, 16, 32, 2, 2, 65),     # all sixteen feature columns
+    (2, 7, 64, 1, 1, 1),       # one token; odd d_phi
+    (3, 6, 128, 1, 3, 129),
+    (3, 6, 32, 1, 9, 4100),    # more tiles than partials: workgroups of several tiles
+])
+def test_feature_map_tile_edges(F, dphi, d, B, H, N):
+    t, phi = wl.make_raw_inputs(3200 + N + d, B, H, N, d, F, dphi, torch.float32)
+    gpu = pu.run_gpu(t, F, dphi, 1e-6, phi=phi, path=hla.HLA_PATH_GENERIC, weight_grads=True)
+    ref = pu.run_oracle(t, F, dphi, 1e-6, phi=phi, weight_grads=True)
+    what = f"f32 maps F={F} dphi={dphi} d={d} N={N}"
+    if N == 1:  # every gradient but dV is what two cancelling terms leave behind
+        scale = pu.short_sequence_rows(t, ref, [0, 1])
+        pu.assert_parity(gpu, ref, 1e-4, what, row_scale=scale)
+        return
+    pu.assert_parity(gpu, ref, 1e-4, what)
+    pu.assert_weight_grad_parity(gpu["wg"], ref["wg"], 1e-4, what)
