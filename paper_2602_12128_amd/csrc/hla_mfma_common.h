@@ -66,6 +66,19 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const void* lds_ptr) {
   return __builtin_bit_cast(u32x2, v);
 }
 
+// 16 bytes per lane from global memory straight to LDS: lane l's piece lands at lds + 16 l (lds is the
+// wave's, not the lane's, address).  Nothing passes through registers; wait_lds_loads() before the
+// barrier behind which other waves read it.
+// Written as assembly because the compiler, unable to tell the buffers apart, makes every later LDS
+// read wait for such a load; it does not count it either, which only makes its own vmcnt waits stricter.
+__device__ __forceinline__ void load_to_lds16(const void* src, unsigned char* lds) {
+  typedef __attribute__((address_space(3))) unsigned char* lptr;
+  const uint32_t at = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)lds)));
+  // M0 holds the LDS address; one wait state between writing it and a load that uses it
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src));
+}
+__device__ __forceinline__ void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // The wave's index in its workgroup as a scalar: what is derived from it (tile numbers, their
 // decoding into batch row / head / token with integer divisions, LDS region bases) then runs on
 // the scalar unit instead of costing vector-ALU slots in every lane.

@@ -636,227 +636,279 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_bwd(Geom g, View Q, View K,
 // ---- weight gradients ---------------------------------------------------------------------------
 // dW1 = X^T dh, db1 = sum dh, dW2 = GELU(h)^T du, db2 = sum du over tokens, for one map per
 // workgroup (blockIdx.y) and, with per-head weights, one head (blockIdx.z).  Both products contract
-// over TOKENS, while the forward layout keeps a token in an MFMA column, so every 32-token tile
-// goes through two wave-private LDS tiles, [token][input channels | du] and [token][dh | GELU(h)],
-// that are read back with transpose reads as operands whose k index is the token.
-// Wave w of the workgroup owns hidden block hb = w % (D/32) -- its first-layer weights stay in
-// registers, it needs no LDS copy of W1 -- and serves the 32-token tiles th, th + T, .. of the
-// workgroup's share, th = w / (D/32), T = WAVES / (D/32).  Its sums end as the hidden-block
-// columns of partial number blockIdx.x * T + th of this (map, head):
+// over TOKENS, so here, unlike in the other kernels, a token is an MFMA *row* of the hidden layer:
+// hidden[tok x hid] = X W1 (A = X rows, B = rows of W1^T: the same operand images) leaves a hidden
+// unit in a lane with its tokens in the accumulator registers, which is what the contractions want
+// as operand: GELU(h) and dh go from the accumulators into the MFMAs without touching LDS.
+// Wave w of the workgroup owns hidden block hb = w % (D/32) (its first-layer weights stay in
+// registers) and serves the 64-token tiles of group w / (D/32).  The waves of a group share the
+// tile in LDS: X in rows (first-layer operand by 16-byte reads, X^T by transpose reads), loaded from
+// memory straight to LDS a tile ahead, and du in bf16; three buffers, one barrier per tile.  Workgroups
+// of four waves, two per compute unit, so that the waves of a SIMD do not meet at the same barrier.
+// A group's sums end as partial number blockIdx.x * T + group of this (map, head):
 //   [dW1 D*D | db1 D | dW2 D*d_phi | db2 d_phi] floats, scaled by the packing factors
 // (dW1, db1 four times too large, dW2 four times too small); a second kernel adds the partials.
-// A workgroup has eight waves, two per SIMD (the live set is kept to 256 registers), and a wave
-// takes one tile per iteration, its steps one after the other: what hides the LDS round trip
-// between writing a tile and reading it back transposed is the other wave of the SIMD.  (A
-// four-wave form with a software pipeline inside the wave -- first layer of tile t+1 and
-// contractions of tile t-1 under the vector work of tile t, two sets of LDS tiles, 352 registers --
-// took 335 us where this one takes 270, 274 against 235 for twelve features per map.)
+// At 12 heads x 128 channels, three factors (us, same box): 76 at 12600 tokens, 175 at 32760; a form
+// that kept tokens in columns and took X, dh and GELU(h) of every wave through LDS and back needed
+// 105 and 247.  The vector ALU (GELU and GELU', 250 instructions per 32 tokens and hidden block) is
+// busy 53 % of the time, the matrix pipe 33 %, the two at once 12 %; finer interleaving changes nothing.
 template <int D>
 struct WgSmem {
-  static constexpr int kXStride = (D + 32) * 2 + 32;  // bytes per token row: channels, 32 du columns, pad
-  static constexpr int kGStride = 64 * 2 + 32;        // dh (32 columns), GELU(h) (32 columns), pad
-  static constexpr int kXBytes = 32 * kXStride;
-  static constexpr int kWaveBytes = kXBytes + 32 * kGStride;  // a wave's two tiles
+  static constexpr int kTok = 64;
+  static constexpr int kX = kTok * D * 2;             // [token][channels], chunks swizzled (tile_off)
+  static constexpr int kDu = kTok * 32;               // [token][16] bf16
+  static constexpr int kBuf = kX + kDu;               // one buffer of one group
+  static constexpr int kBufs = 3;
 };
 
 template <int D, int WAVES, int DPH>
-__global__ __launch_bounds__(WAVES * 64) void k_phi_wgrad(Geom g, View Q, View K,
-                                                          const unsigned char* __restrict__ wpk,
-                                                          int heads_w,
-                                                          const float* __restrict__ feat,
-                                                          const float* __restrict__ dfeat,
-                                                          float* __restrict__ partial) {
+__global__ __launch_bounds__(WAVES * 64, 2) void k_phi_wgrad(Geom g, View Q, View K,
+                                                             const unsigned char* __restrict__ wpk,
+                                                             int heads_w,
+                                                             const float* __restrict__ dfeat,
+                                                             float* __restrict__ partial) {
   using SM = WgSmem<D>;
   using PK = Packed<D>;
   constexpr int NRB = D / 32, NKS = D / 16, TH = WAVES / NRB;
   static_assert(WAVES % NRB == 0, "whole groups of hidden blocks");
-  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int kPieces = D / 8;                        // 16-byte pieces per row
+  constexpr int kLoads = SM::kTok * kPieces / (NRB * 64);  // of a lane, per tile
+  constexpr int kPairs = DPH / 2, kDuLoads = (kPairs + NRB - 1) / NRB;
+  extern __shared__ __align__(256) unsigned char smem[];
   const int lane = threadIdx.x % kWave, wave = wave_index();
   const int r = lane % 32, gl = lane / 32;
   const int L = lane % 16, q = lane / 16;
-  const int hb = wave % NRB, th = wave / NRB;
+  const int hb = wave % NRB, grp = wave / NRB;
   const int m = blockIdx.y, hw = blockIdx.z;
-  unsigned char* xt = smem + wave * SM::kWaveBytes;  // this wave's (X tile, G tile)
-  unsigned char* gt = xt + SM::kXBytes;
+  unsigned char* bufs = smem + grp * SM::kBufs * SM::kBuf;
   const unsigned char* wm = wpk + (static_cast<int64_t>(m) * heads_w + hw) * PK::kBytes;
   const View& X = m == 0 ? Q : K;
   // this wave's first-layer operands: rows 32 hb + r of W1^T, k-slot (ks, gl, j) = channel 16ks + 8gl + j
-  u32x4 w1a[NKS];
+  u32x4 w1b[NKS];
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks)
-    w1a[ks] = *reinterpret_cast<const u32x4*>(wm + PK::kW1T + ((32 * hb + r) * D + 16 * ks + 8 * gl) * 2);
+    w1b[ks] = *reinterpret_cast<const u32x4*>(wm + PK::kW1T + ((32 * hb + r) * D + 16 * ks + 8 * gl) * 2);
   const u32x4 w2b = *reinterpret_cast<const u32x4*>(wm + PK::kW2B + (hb * 64 + lane) * 16);
-  f32x16 bias;  // first-layer bias of the block in accumulator order
+  f32x16 bias;  // of hidden unit 32 hb + r, for every token
   {
-    const float* b1 = reinterpret_cast<const float*>(wm + PK::kB1) + 32 * hb + 4 * gl;
+    const float bv = *reinterpret_cast<const float*>(wm + PK::kB1 + (32 * hb + r) * 4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f32x4 bv = *reinterpret_cast<const f32x4*>(b1 + 8 * i);
-      bias[4 * i] = bv[0];
-      bias[4 * i + 1] = bv[1];
-      bias[4 * i + 2] = bv[2];
-      bias[4 * i + 3] = bv[3];
-    }
+    for (int i = 0; i < 16; ++i) bias[i] = bv;
   }
   // token tiles: one list over all (batch row, head) pairs when the weights are shared
   const bool shared = heads_w == 1;
-  const int tpr = (g.N + 31) / 32;
+  const int tpr = (g.N + SM::kTok - 1) / SM::kTok;
   const int total = (shared ? g.B * g.H : g.B) * tpr;
-  f32x16 acc[NRB];   // dW1 rows 32 ib + d_row(i, gl), column 32 hb + r
-  f32x16 acc2;       // dW2^T rows = features d_row(i, gl), column 32 hb + r
-  float db1[16];     // per-lane (token r) sums of dh for hidden 32 hb + d_row(i, gl)
-  float db2[DPH];    // per-lane sums of du (read from the lanes gl == 0)
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-#pragma unroll
-    for (int ib = 0; ib < NRB; ++ib) acc[ib][i] = 0.0f;
-    acc2[i] = 0.0f;
-    db1[i] = 0.0f;
-  }
-#pragma unroll
-  for (int a = 0; a < DPH; ++a) db2[a] = 0.0f;
-  // The next tile's inputs are loaded as soon as the current tile's have been consumed (the
-  // input rows after the copy to LDS, the features once du is formed).  These loads are
-  // unconditional with clamped addresses, so that the same number is outstanding on every path;
-  // the last tile is simply fetched twice.
-  const int step = gridDim.x * TH;
-  int tile = blockIdx.x * TH + th;
-  u32x4 xb[NKS];  // input rows of the coming tile
-  float fv[DPH], dv[DPH];
-  auto coords = [&](int t, int& b, int& h, int& n0) {
-    const int row = t / tpr;
-    n0 = (t % tpr) * 32;
-    b = shared ? row / g.H : row;
-    h = shared ? row % g.H : hw;
-  };
-  auto fetch_features = [&](int b, int h, int n0) {
-    const int n = n0 + r;
-    const int64_t o = g.fidx(g.th(b, h, n < g.N ? n : g.N - 1), m * DPH);
-    const f32x2* fp = reinterpret_cast<const f32x2*>(feat + o);
-    const f32x2* dp = reinterpret_cast<const f32x2*>(dfeat + o);
-#pragma unroll
-    for (int p = 0; p < DPH / 2; ++p) {
-      const f32x2 f2 = fp[32 * p], d2 = dp[32 * p];
-      fv[2 * p] = f2[0];
-      fv[2 * p + 1] = f2[1];
-      dv[2 * p] = d2[0];
-      dv[2 * p + 1] = d2[1];
-    }
-  };
-  // du of the token: zero where the ReLU was closed, and for tokens past the end (whose clamped
-  // input row then adds nothing to any sum).  As the B operand of dg = W2 du^T, slot (gl, j) is
-  // feature 8 gl + j: with d_phi <= 8 the lanes gl = 1 hold zeros throughout (db2 included), with
-  // more features they hold the ninth feature on.
-  auto make_du = [&](bool live, u32x4& dub) {
-    float du[DPH];
-#pragma unroll
-    for (int a = 0; a < DPH; ++a) du[a] = live && (DPH > 8 || gl == 0) && fv[a] > 0.0f ? dv[a] : 0.0f;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const float lo0 = 2 * p < DPH ? du[2 * p < DPH ? 2 * p : 0] : 0.0f;
-      const float hi0 = 2 * p + 1 < DPH ? du[2 * p + 1 < DPH ? 2 * p + 1 : 0] : 0.0f;
-      const float lo1 = 8 + 2 * p < DPH ? du[8 + 2 * p < DPH ? 8 + 2 * p : 0] : 0.0f;
-      const float hi1 = 9 + 2 * p < DPH ? du[9 + 2 * p < DPH ? 9 + 2 * p : 0] : 0.0f;
-      dub[p] = DPH > 8 ? pack_bf16(gl ? lo1 : lo0, gl ? hi1 : hi0) : pack_bf16(lo0, hi0);
-    }
-#pragma unroll
-    for (int a = 0; a < DPH; ++a) db2[a] += du[a];
-  };
-  auto put_x_tile = [&](unsigned char* xdst, const u32x4 (&xr)[NKS], const u32x4& dub) {  // [token][channels | du]
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks)
-      *reinterpret_cast<u32x4*>(xdst + r * SM::kXStride + (16 * ks + 8 * gl) * 2) = xr[ks];
-    u32x4 z4;
-    z4[0] = z4[1] = z4[2] = z4[3] = 0u;
-    // du columns D + 8 gl .. + 7 are this lane's operand slots; columns D + 16 .. D + 31 are zero
-    *reinterpret_cast<u32x4*>(xdst + r * SM::kXStride + (D + 8 * gl) * 2) = dub;
-    *reinterpret_cast<u32x4*>(xdst + r * SM::kXStride + (D + 16 + 8 * gl) * 2) = z4;
-  };
-  // transpose-read operand: tokens 16 ks + 8 gl + {0..7} of 32 columns starting at col0
-  auto operand = [&](const unsigned char* tl, int stride, int ks, int col0) {
-    const int krow = 16 * ks + 8 * gl + L / 4;
-    const unsigned char* p = tl + krow * stride + (col0 + 16 * (q % 2) + 4 * (L % 4)) * 2;
-    const u32x2 lo = lds_read_tr16(p);
-    const u32x2 hi = lds_read_tr16(p + 4 * stride);
-    u32x4 o;
-    o[0] = lo[0];
-    o[1] = lo[1];
-    o[2] = hi[0];
-    o[3] = hi[1];
-    return o;
-  };
   f32x16 zero;
 #pragma unroll
   for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
-  // One tile per iteration, its steps one after the other (first layer, dg, the two LDS tiles,
-  // GELU and GELU', the contractions over its tokens): the second wave of the SIMD runs while this
-  // one waits.  xb, fv, dv always hold the coming tile, loaded as soon as the current tile has used them.
-  // (with more than eight features per map the feature loads are not run ahead: their registers
-  // are what makes the difference between fitting 256 and spilling)
-  constexpr bool kFeatAhead = DPH <= 8;
-  if (tile < total) {
-    int b, h, n0;
-    coords(tile, b, h, n0);
-    load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
-    if (kFeatAhead) fetch_features(b, h, n0);
+  f32x16 acc[NRB];   // dW1 rows 32 ib + d_row(i, gl), column 32 hb + r
+  f32x16 acc2 = zero;  // dW2^T rows = features d_row(i, gl), column 32 hb + r
+  float db1 = 0.0f;  // of hidden unit 32 hb + r, over the lane half's tokens
+  float db2[2 * kDuLoads];  // of the features this wave loads, over the lane's tokens
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib) acc[ib] = zero;
+#pragma unroll
+  for (int a = 0; a < 2 * kDuLoads; ++a) db2[a] = 0.0f;
+  // columns d_phi .. 15 of the du tiles stay zero
+  for (int i = threadIdx.x; i < TH * SM::kBufs * SM::kDu / 16; i += WAVES * 64) {
+    u32x4 z4;
+    z4[0] = z4[1] = z4[2] = z4[3] = 0u;
+    const int b = i / (SM::kDu / 16);
+    *reinterpret_cast<u32x4*>(smem + b * SM::kBuf + SM::kX + (i % (SM::kDu / 16)) * 16) = z4;
   }
-  for (; tile < total; tile += step) {
-    int b, h, n0;
-    coords(tile, b, h, n0);
-    if (!kFeatAhead) fetch_features(b, h, n0);
-    u32x4 dub;
-    make_du(n0 + r < g.N, dub);
-    f32x16 cur = bias;
+  __syncthreads();
+  f32x2 dr[kDuLoads];
+  bool du_live = false;
+  // Start the loads of one tile: this wave's share of the X rows straight to LDS (16 bytes per lane to
+  // consecutive places, so the lane fetches the piece that the swizzle puts there), its share of du to
+  // registers.  Every address is valid (tiles past the list re-read the last, rows past the sequence
+  // its last row); what must not count is zeroed in du.
+  auto fetch = [&](int tile, unsigned char* buf) {
+    const int tc = tile < total ? tile : total - 1;
+    const int row = tc / tpr, n0 = (tc % tpr) * SM::kTok;
+    const int b = shared ? row / g.H : row, h = shared ? row % g.H : hw;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) cur = mfma32(w1a[ks], xb[ks], cur);
-    const f32x16 dg = mfma32(w2b, dub, zero);
-    put_x_tile(xt, xb, dub);
-    {
-      const int tn = tile + step < total ? tile + step : tile;
-      coords(tn, b, h, n0);
-      load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
-      if (kFeatAhead) fetch_features(b, h, n0);
+    for (int i = 0; i < kLoads; ++i) {
+      const int pos = (hb * kLoads + i) * 64 + lane, t = pos / kPieces;
+      const int piece = (pos % kPieces) ^ (tile_swz<D * 2>(t) & (kPieces - 1));
+      const int n = n0 + t;
+      load_to_lds16(X.row<const bf16_t>(b, h, n < g.N ? n : g.N - 1) + 8 * piece, buf + (hb * kLoads + i) * 1024);
     }
+    const int n = n0 + lane;
+    du_live = tile < total && n < g.N;
+    const f32x2* dp = reinterpret_cast<const f32x2*>(dfeat + g.fidx(g.th(b, h, n < g.N ? n : g.N - 1), m * DPH));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {  // slice j covers hidden 8j + 4gl .. +3 of the block
-      const float in[4] = {cur[4 * j], cur[4 * j + 1], cur[4 * j + 2], cur[4 * j + 3]};
-      f16x2 gv[2], gp[2];
-      gelu_both_f16<2>(in, gv, gp);
-      const float d0 = __builtin_fmaf(static_cast<float>(gp[0][0]), dg[4 * j], 0.0f);
-      const float d1 = __builtin_fmaf(static_cast<float>(gp[0][1]), dg[4 * j + 1], 0.0f);
-      const float d2 = __builtin_fmaf(static_cast<float>(gp[1][0]), dg[4 * j + 2], 0.0f);
-      const float d3 = __builtin_fmaf(static_cast<float>(gp[1][1]), dg[4 * j + 3], 0.0f);
-      db1[4 * j] += d0;
-      db1[4 * j + 1] += d1;
-      db1[4 * j + 2] += d2;
-      db1[4 * j + 3] += d3;
-      u32x2 dh2, g2;
-      dh2[0] = pack_bf16(d0, d1);
-      dh2[1] = pack_bf16(d2, d3);
-      g2[0] = pack_bf16(static_cast<float>(gv[0][0]), static_cast<float>(gv[0][1]));
-      g2[1] = pack_bf16(static_cast<float>(gv[1][0]), static_cast<float>(gv[1][1]));
-      *reinterpret_cast<u32x2*>(gt + r * SM::kGStride + (8 * j + 4 * gl) * 2) = dh2;
-      *reinterpret_cast<u32x2*>(gt + r * SM::kGStride + (32 + 8 * j + 4 * gl) * 2) = g2;
+    for (int i = 0; i < kDuLoads; ++i) {
+      const int p = hb * kDuLoads + i;
+      dr[i] = dp[32 * (p < kPairs ? p : 0)];
     }
-    wave_lds_sync();
+  };
+  auto put_du = [&](unsigned char* buf) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const u32x4 bdh = operand(gt, SM::kGStride, ks, 0);
-      const u32x4 bg = operand(gt, SM::kGStride, ks, 32);
-      u32x4 ax[NRB + 1];
-#pragma unroll
-      for (int ib = 0; ib < NRB; ++ib) ax[ib] = operand(xt, SM::kXStride, ks, 32 * ib);
-      ax[NRB] = operand(xt, SM::kXStride, ks, D);
-#pragma unroll
-      for (int ib = 0; ib < NRB; ++ib) acc[ib] = mfma32(ax[ib], bdh, acc[ib]);
-      acc2 = mfma32(ax[NRB], bg, acc2);
+    for (int i = 0; i < kDuLoads; ++i) {
+      const int p = hb * kDuLoads + i;
+      if (p < kPairs) {
+        const float d0 = du_live ? dr[i][0] : 0.0f, d1 = du_live ? dr[i][1] : 0.0f;
+        db2[2 * i] += d0;
+        db2[2 * i + 1] += d1;
+        *reinterpret_cast<uint32_t*>(buf + SM::kX + lane * 32 + p * 4) = pack_bf16(d0, d1);
+      }
     }
-    wave_lds_sync();  // the tiles are free for the next tile
+  };
+  // LDS addresses.  First layer: row r, chunk 2 ks + gl.  Transpose reads of X^T: k-slot (gl, j) of
+  // step ks is token 16 ks + 8 (j / 4) + 4 gl + j % 4, the order the accumulators hold.  Swizzling
+  // ignores the row's bits 4 and up: sub-tiles and steps add constants.
+  int a_off[NKS], t_off[2][NRB];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) a_off[ks] = tile_off<D * 2>(r, 2 * ks + gl);
+#pragma unroll
+  for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) {
+      const int row = 4 * gl + 8 * hi + L / 4, col = 32 * ib + 16 * (q % 2) + 4 * (L % 4);
+      t_off[hi][ib] = tile_off<D * 2>(row, col >> 3) + ((col & 7) << 1);
+    }
+  const int du_a = SM::kX + r * 32 + gl * 16;                          // operand of dg: token r, features 8 gl ..
+  const int du_t = SM::kX + (4 * gl + L / 4) * 32 + 8 * (L % 4);  // of dW2^T; rows past the sixteenth feature repeat: never stored
+  // A operand number x of the contraction over tokens 16 ks .. + 15 of a sub-tile: X^T block x, or du^T
+  auto tn_operand = [&](const unsigned char* buf, int sub, int ks, int x) {
+    const unsigned char* lo_p = x < NRB ? buf + (32 * sub + 16 * ks) * D * 2 + t_off[0][x < NRB ? x : 0]
+                                        : buf + (32 * sub + 16 * ks) * 32 + du_t;
+    const unsigned char* hi_p = x < NRB ? buf + (32 * sub + 16 * ks) * D * 2 + t_off[1][x < NRB ? x : 0]
+                                        : buf + (32 * sub + 16 * ks + 8) * 32 + du_t;
+    const u32x2 lo = lds_read_tr16(lo_p), hi = lds_read_tr16(hi_p);
+    u32x4 a;
+    a[0] = lo[0];
+    a[1] = lo[1];
+    a[2] = hi[0];
+    a[3] = hi[1];
+    return a;
+  };
+  constexpr int kPer = NKS / 4;       // first-layer MFMAs per slice
+  constexpr int NX = NRB + 1;         // operands of a contraction step
+  constexpr int kSplit = (NX + 1) / 2;  // of them in its first slice
+  u32x4 an[kPer], ct[kSplit], dua;
+  u32x4 dhp, gvp;                     // dh, GELU of the previous sub-tile's second step
+  f32x16 hb2[2];                      // hidden blocks of this and the next sub-tile
+  // One 32-token sub-tile: GELU and GELU' on the vector ALU in four slices; between them the matrix
+  // pipe does the next sub-tile's first layer, the previous one's second contraction step (slices 0,
+  // 1) and this one's first (slices 2, 3), operands read a slice ahead.
+  auto sub_tile = [&](auto PAR, const unsigned char* cur_b, int sub, const unsigned char* nxt_b, int nsub,
+                      const unsigned char* prv_b, int psub) {
+    constexpr int par = decltype(PAR)::value;
+    f32x16& cur = hb2[par];
+    f32x16& nxt = hb2[1 - par];
+    const f32x16 dg = mfma32(dua, w2b, zero);
+    u32x4 dh[2], gv[2];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int t = 0; t < kPer; ++t) {
+        nxt = mfma32(an[t], w1b[j * kPer + t], j == 0 && t == 0 ? bias : nxt);
+        an[t] = j < 3 ? *reinterpret_cast<const u32x4*>(nxt_b + nsub * 32 * D * 2 + a_off[((j + 1) % 4) * kPer + t]) : an[t];
+      }
+      if (j == 3) dua = *reinterpret_cast<const u32x4*>(nxt_b + nsub * 32 * 32 + du_a);
+      {
+        constexpr int half[2] = {0, kSplit};
+        const int x0 = half[j % 2], x1 = j % 2 == 0 ? kSplit : NX;
+        const u32x4 bd = j < 2 ? dhp : dh[0], bg = j < 2 ? gvp : gv[0];
+#pragma unroll
+        for (int x = x0; x < x1; ++x) {
+          if (x < NRB)
+            acc[x < NRB ? x : 0] = mfma32(ct[x - x0], bd, acc[x < NRB ? x : 0]);
+          else
+            acc2 = mfma32(ct[x - x0], bg, acc2);
+        }
+        // the next slice's operands: second half of the same step, or the next step's first half
+        const int y0 = half[(j + 1) % 2], y1 = (j + 1) % 2 == 0 ? kSplit : NX;
+#pragma unroll
+        for (int y = y0; y < y1; ++y)
+          ct[y - y0] = j == 0 ? tn_operand(prv_b, psub, 1, y) : (j < 3 ? tn_operand(cur_b, sub, 0, y) : tn_operand(cur_b, sub, 1, y));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      {
+        const int ks = j / 2, jj = j % 2, i0 = 4 * j;  // accumulator registers of tokens 16 ks + 8 jj + 4 gl + 0..3
+        const float in[4] = {cur[i0], cur[i0 + 1], cur[i0 + 2], cur[i0 + 3]};
+        f16x2 gg[2], gp[2];
+        gelu_both_f16<2>(in, gg, gp);
+        const float d0 = __builtin_fmaf(static_cast<float>(gp[0][0]), dg[i0], 0.0f);
+        const float d1 = __builtin_fmaf(static_cast<float>(gp[0][1]), dg[i0 + 1], 0.0f);
+        const float d2 = __builtin_fmaf(static_cast<float>(gp[1][0]), dg[i0 + 2], 0.0f);
+        const float d3 = __builtin_fmaf(static_cast<float>(gp[1][1]), dg[i0 + 3], 0.0f);
+        db1 += (d0 + d1) + (d2 + d3);
+        asm volatile("" : "+v"(db1));  // summed here, not with the terms kept until the next tile
+        dh[ks][2 * jj] = pack_bf16(d0, d1);
+        dh[ks][2 * jj + 1] = pack_bf16(d2, d3);
+        gv[ks][2 * jj] = pack_bf16(static_cast<float>(gg[0][0]), static_cast<float>(gg[0][1]));
+        gv[ks][2 * jj + 1] = pack_bf16(static_cast<float>(gg[1][0]), static_cast<float>(gg[1][1]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    dhp = dh[1];
+    gvp = gv[1];
+    // the coming sub-tile's next one: its first-layer operands are read by the caller's next call
+  };
+  const int step = gridDim.x * TH;
+  const int first = blockIdx.x * TH;
+  const int iters = (total - first + step - 1) / step;  // of group 0, which has the most
+  fetch(first + grp, bufs);
+  put_du(bufs);
+  fetch(first + step + grp, bufs + SM::kBuf);
+  wait_lds_loads();
+  __syncthreads();
+  // hidden block of the first sub-tile, and what its first slice needs
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks)
+    hb2[0] = mfma32(*reinterpret_cast<const u32x4*>(bufs + a_off[ks]), w1b[ks], ks == 0 ? bias : hb2[0]);
+  dua = *reinterpret_cast<const u32x4*>(bufs + du_a);
+  dhp[0] = dhp[1] = dhp[2] = dhp[3] = 0u;  // nothing before the first sub-tile
+  gvp = dhp;
+#pragma unroll
+  for (int x = 0; x < kSplit; ++x) ct[x] = tn_operand(bufs, 0, 1, x);
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) an[t] = *reinterpret_cast<const u32x4*>(bufs + 32 * D * 2 + a_off[t]);
+  // Tile `it` sits in buffer it % 3.  Its second sub-tile already needs the next tile: the barrier in
+  // front of it comes after every wave's loads of that tile have landed, and says that the tile
+  // before this one is done with, whose buffer takes the loads of the tile after next.
+  auto tile_step = [&](auto B, int it) {
+    constexpr int b = decltype(B)::value;
+    unsigned char* cb = bufs + b * SM::kBuf;
+    unsigned char* nb = bufs + ((b + 1) % 3) * SM::kBuf;
+    unsigned char* pb = bufs + ((b + 2) % 3) * SM::kBuf;
+    sub_tile(std::integral_constant<int, 0>{}, cb, 0, cb, 1, it == 0 ? cb : pb, it == 0 ? 0 : 1);
+    put_du(nb);
+    wait_lds_loads();
+    __syncthreads();
+    fetch(first + (it + 2) * step + grp, pb);
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) an[t] = *reinterpret_cast<const u32x4*>(nb + a_off[t]);
+    sub_tile(std::integral_constant<int, 1>{}, cb, 1, nb, 0, cb, 0);
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) an[t] = *reinterpret_cast<const u32x4*>(nb + 32 * D * 2 + a_off[t]);
+  };
+  for (int it = 0; it < iters; it += 3) {
+    tile_step(std::integral_constant<int, 0>{}, it);
+    if (it + 1 < iters) tile_step(std::integral_constant<int, 1>{}, it + 1);
+    if (it + 2 < iters) tile_step(std::integral_constant<int, 2>{}, it + 2);
   }
-  // ---- this wave's share of the partial
+  // the last sub-tile's second contraction step: its operands are in ct (first half) and LDS
+  {
+    const unsigned char* lb = bufs + ((iters - 1) % 3) * SM::kBuf;
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      const u32x4 a = x < kSplit ? ct[x] : tn_operand(lb, 1, 1, x);
+      if (x < NRB)
+        acc[x < NRB ? x : 0] = mfma32(a, dhp, acc[x < NRB ? x : 0]);
+      else
+        acc2 = mfma32(a, gvp, acc2);
+    }
+  }
+  // ---- this wave's share of the partial (fetches past the list counted as zero)
   const int nparts = gridDim.x * TH;
   const int64_t floats = static_cast<int64_t>(D) * D + D + D * DPH + DPH;
-  float* out = partial + ((static_cast<int64_t>(m) * gridDim.z + hw) * nparts + blockIdx.x * TH + th) * floats;
+  float* out = partial + ((static_cast<int64_t>(m) * gridDim.z + hw) * nparts + blockIdx.x * TH + grp) * floats;
 #pragma unroll
   for (int ib = 0; ib < NRB; ++ib)
 #pragma unroll
@@ -866,21 +918,19 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_wgrad(Geom g, View Q, View K
     const int a = d_row(i, gl);
     if (a < DPH) out[D * D + D + (32 * hb + r) * DPH + a] = acc2[i];
   }
-  // sums over the 32 tokens of a half-wave (xor offsets below 32 stay inside it)
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float v = db1[i];
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (r == 0) out[D * D + 32 * hb + d_row(i, gl)] = v;
+  {
+    const float v = db1 + partner32(db1);
+    if (gl == 0) out[D * D + 32 * hb + r] = v;
   }
-  if (hb == 0) {
 #pragma unroll
-    for (int a = 0; a < DPH; ++a) {
-      float v = db2[a];
+  for (int i = 0; i < kDuLoads; ++i) {
+    const int p = hb * kDuLoads + i;
 #pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0) out[D * D + D + D * DPH + a] = v;
+    for (int e = 0; e < 2; ++e) {
+      float v = db2[2 * i + e];
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+      if (lane == 0 && p < kPairs) out[D * D + D + D * DPH + 2 * p + e] = v;
     }
   }
 }
@@ -938,29 +988,28 @@ hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
   return HLA_OK;
 }
 
-constexpr int kWavesW = 8;  // two waves per SIMD
+constexpr int kWavesW = 4;  // two workgroups per compute unit: their barriers leave each other alone
 
 template <int D, int DPH>
 hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
   using SM = WgSmem<D>;
   constexpr int TH = kWavesW / (D / 32);
-  constexpr int lds = kWavesW * SM::kWaveBytes;  // a set of tiles per wave
+  constexpr int lds = TH * SM::kBufs * SM::kBuf;
   Geom g = hd->g;
   const unsigned char* wpk = static_cast<const unsigned char*>(hd->path_ws) + hd->w_packed_off;
   const int nm = 1 + g.F;
   const bool shared = hd->phi.heads_w == 1;
   const int heads = shared ? 1 : g.H;
-  const int64_t tiles = static_cast<int64_t>(shared ? g.B * g.H : g.B) * ((g.N + 31) / 32);
+  const int64_t tiles = static_cast<int64_t>(shared ? g.B * g.H : g.B) * ((g.N + SM::kTok - 1) / SM::kTok);
   // one workgroup per compute unit in total, each with at least one tile per wave group
-  int64_t nblk = 256 / (static_cast<int64_t>(nm) * heads);
+  int64_t nblk = 512 / (static_cast<int64_t>(nm) * heads);
   if (nblk > (tiles + TH - 1) / TH) nblk = (tiles + TH - 1) / TH;
   if (nblk < 1) nblk = 1;
   const int64_t nparts = nblk * TH;
   if (nm * heads * nparts > hd->wg_parts_cap) return HLA_ERR_STATE;
   HLA_TRY(launch(hd, "mfma_phi_weight_grads", k_phi_wgrad<D, kWavesW, DPH>,
                  dim3(static_cast<unsigned>(nblk), nm, heads), dim3(kWavesW * 64), lds, a.stream, g, a.Q, a.K,
-                 wpk, hd->phi.heads_w, static_cast<const float*>(hd->feat),
-                 static_cast<const float*>(hd->dfeat), hd->wg_partial));
+                 wpk, hd->phi.heads_w, static_cast<const float*>(hd->dfeat), hd->wg_partial));
   // undo the packing factors: dh and dg carry 1/kHiddenScale, GELU(h) carries kHiddenScale
   return weight_grads_reduce(hd, static_cast<int>(nparts), heads, kHiddenScale, kHiddenScale,
                              1.0f / kHiddenScale, 1.0f, a.stream);
@@ -970,7 +1019,7 @@ template <int D, int F, int DPH>
 hla_status prepare_t() {
   HLA_TRY(allow_lds(&k_phi_fwd<D, F, kWavesF, DPH>, PhiSmem<D>::total(F, kWavesF)));
   HLA_TRY(allow_lds(&k_phi_bwd<D, F, kWavesB, DPH>, PhiSmem<D, true>::total(F, kWavesB)));
-  return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, kWavesW * WgSmem<D>::kWaveBytes);
+  return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, kWavesW / (D / 32) * WgSmem<D>::kBufs * WgSmem<D>::kBuf);
 }
 
 }  // namespace
