@@ -33,8 +33,8 @@ struct FalseTag {
 template <int D>
 struct Packed {
   static constexpr int kW1T = 0;                      // bf16 [D][D]: row = hidden unit, col = input channel; times 1/4
-  static constexpr int kW2A = kW1T + D * D * 2;       // fp16 [D/16][64][8]: A operand of u^T = W2^T g^T; times 4
-  static constexpr int kW2B = kW2A + D * 32 * 2;      // bf16 [D/32][64][8]: A operand of dg^T = W2 du^T; times 4
+  static constexpr int kW2A = kW1T + D * D * 2;       // fp16 [D/16][32][8]: A operand of u^T = W2^T g^T (16 rows); times 4
+  static constexpr int kW2B = kW2A + D * 16 * 2;      // bf16 [D/32][64][8]: A operand of dg^T = W2 du^T; times 4
   static constexpr int kB1 = kW2B + D * 16 * 2;       // fp32 [D]; times 1/4
   static constexpr int kB2 = kB1 + D * 4;             // fp32 [16]
   static constexpr int kBytes = kB2 + 64;
@@ -62,9 +62,8 @@ __global__ void k_pack_phi(PhiF32 w, int dphi, unsigned char* __restrict__ out) 
     const int hid = i / D, in = i % D;
     w1t[i] = f32_to_bf16_bits(kHiddenScale * W1[in * D + hid]);
   }
-  for (int i = threadIdx.x; i < (D / 16) * 512; i += blockDim.x) {
-    const int ks2 = i / 512, lane = (i / 8) % 64, j = i % 8;
-    const int r = lane % 32, gl = lane / 32;
+  for (int i = threadIdx.x; i < (D / 16) * 256; i += blockDim.x) {
+    const int ks2 = i / 256, gl = (i / 128) % 2, r = (i / 8) % 16, j = i % 8;
     const int n = hidden_of_slot(ks2, gl, j);
     w2a[i] = r < dphi ? __builtin_bit_cast(uint16_t, static_cast<_Float16>(W2[n * dphi + r] / kHiddenScale)) : 0;
   }
@@ -88,11 +87,11 @@ struct PhiSmem {
   static constexpr int kChunks = D / 8;               // 16-byte chunks per row
   static constexpr int kRow = D * 2;                  // bytes per row
   static constexpr int kW1 = D * D * 2;
-  static constexpr int kW2 = BACKWARD ? D * 16 * 2 : D * 32 * 2;  // W2B (backward) or W2A (forward)
+  static constexpr int kW2 = D * 16 * 2;              // W2B (backward) or W2A (forward)
   static constexpr int kMap = kW1 + kW2 + D * 4 + 64;  // then b1 [D] and b2 [16] in fp32
-  // backward adds a 16-row transpose tile per wave for whole-row stores of dX
+  // backward adds a 16-row transpose tile per wave for whole-row stores of dX, forward the list's counter
   static constexpr int total(int nmaps, int waves) {
-    return nmaps * kMap + (BACKWARD ? waves * RowTile<D, 16>::kBytes : 0);
+    return nmaps * kMap + (BACKWARD ? waves * RowTile<D, 16>::kBytes : 16);
   }
   __host__ __device__ static __forceinline__ int swz(int row) {
     return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
@@ -102,39 +101,47 @@ struct PhiSmem {
   }
 };
 
-// Copy the packed weights of NMAPS (map, head) blocks into LDS (all THREADS threads of the
-// workgroup).  All global loads of a map are issued before the first LDS store so that they are
-// in flight together: the copy costs one memory round trip per map instead of one per 16 bytes.
-template <int D, bool BACKWARD, int THREADS>
-__device__ __forceinline__ void load_weights(unsigned char* dst, const unsigned char* src) {
+// Copy the packed weights of NMAPS maps (blocks `step` bytes apart in memory, kMap apart in LDS) into
+// LDS, all THREADS threads of the workgroup.  All global loads are issued before the first LDS store
+// so that they are in flight together: the copy costs one memory round trip, not one per map or piece.
+template <int D, bool BACKWARD, int THREADS, int NMAPS = 1>
+__device__ __forceinline__ void load_weights(unsigned char* dst, const unsigned char* src, int64_t step = 0) {
   using SM = PhiSmem<D, BACKWARD>;
   using PK = Packed<D>;
-  constexpr int N1 = D * SM::kChunks;                              // 16-byte chunks of W1^T
-  constexpr int N2 = (BACKWARD ? D * 16 * 2 : D * 32 * 2) / 16;    // 16-byte chunks of the W2 image
-  constexpr int NB = D + 16;                                       // floats of b1 and b2
+  constexpr int N1 = D * SM::kChunks;              // 16-byte chunks of W1^T
+  constexpr int N2 = SM::kW2 / 16;                 // 16-byte chunks of the W2 image
+  constexpr int NB = D + 16;                       // floats of b1 and b2
   constexpr int I1 = (N1 + THREADS - 1) / THREADS, I2 = (N2 + THREADS - 1) / THREADS;
-  const unsigned char* w2 = src + (BACKWARD ? PK::kW2B : PK::kW2A);
   const int t = threadIdx.x;
-  u32x4 v1[I1], v2[I2];
-  float vb = 0.0f;
+  u32x4 v1[NMAPS][I1], v2[NMAPS][I2];
+  float vb[NMAPS];
 #pragma unroll
-  for (int k = 0; k < I1; ++k)
-    if (N1 % THREADS == 0 || t + k * THREADS < N1) v1[k] = *reinterpret_cast<const u32x4*>(src + PK::kW1T + (t + k * THREADS) * 16);
+  for (int m = 0; m < NMAPS; ++m) {
+    const unsigned char* s = src + m * step;
+    const unsigned char* w2 = s + (BACKWARD ? PK::kW2B : PK::kW2A);
 #pragma unroll
-  for (int k = 0; k < I2; ++k)
-    if (N2 % THREADS == 0 || t + k * THREADS < N2) v2[k] = *reinterpret_cast<const u32x4*>(w2 + (t + k * THREADS) * 16);
-  if (t < NB) vb = *reinterpret_cast<const float*>(src + PK::kB1 + t * 4);
+    for (int k = 0; k < I1; ++k)
+      if (N1 % THREADS == 0 || t + k * THREADS < N1) v1[m][k] = *reinterpret_cast<const u32x4*>(s + PK::kW1T + (t + k * THREADS) * 16);
 #pragma unroll
-  for (int k = 0; k < I1; ++k) {
-    const int i = t + k * THREADS;
-    if (N1 % THREADS == 0 || i < N1) *reinterpret_cast<u32x4*>(dst + SM::off(i / SM::kChunks, i % SM::kChunks)) = v1[k];
+    for (int k = 0; k < I2; ++k)
+      if (N2 % THREADS == 0 || t + k * THREADS < N2) v2[m][k] = *reinterpret_cast<const u32x4*>(w2 + (t + k * THREADS) * 16);
+    vb[m] = t < NB ? *reinterpret_cast<const float*>(s + PK::kB1 + t * 4) : 0.0f;
   }
 #pragma unroll
-  for (int k = 0; k < I2; ++k) {
-    const int i = t + k * THREADS;
-    if (N2 % THREADS == 0 || i < N2) *reinterpret_cast<u32x4*>(dst + SM::kW1 + i * 16) = v2[k];
+  for (int m = 0; m < NMAPS; ++m) {
+    unsigned char* d = dst + m * SM::kMap;
+#pragma unroll
+    for (int k = 0; k < I1; ++k) {
+      const int i = t + k * THREADS;
+      if (N1 % THREADS == 0 || i < N1) *reinterpret_cast<u32x4*>(d + SM::off(i / SM::kChunks, i % SM::kChunks)) = v1[m][k];
+    }
+#pragma unroll
+    for (int k = 0; k < I2; ++k) {
+      const int i = t + k * THREADS;
+      if (N2 % THREADS == 0 || i < N2) *reinterpret_cast<u32x4*>(d + SM::kW1 + i * 16) = v2[m][k];
+    }
+    if (t < NB) *reinterpret_cast<float*>(d + SM::kW1 + SM::kW2 + t * 4) = vb[m];
   }
-  if (t < NB) *reinterpret_cast<float*>(dst + SM::kW1 + SM::kW2 + t * 4) = vb;
 }
 
 // The lane's share of its token's input vector as B operands: k-slot (ks, gl, j) is channel
@@ -191,37 +198,52 @@ __device__ __forceinline__ TileMap make_tile_map(const Geom& g, int heads_w) {
 }
 
 // ---- forward ------------------------------------------------------------------------------------
-// block WAVES*64.  Maps map0 .. map0+NMAPS-1 are applied to X; the features go to the fp32
-// feature workspace.  Wave w of the grid serves 32-token tiles w, w + (total waves), ..; the next
-// tile's inputs are loaded while the current one is computed.
-template <int D, int NMAPS, int WAVES, int DPH>
-__device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
-                                             const unsigned char* __restrict__ wpk, int heads_w,
-                                             int map0, int nmaps, float* __restrict__ feat) {
+// block WAVES*64, three waves per SIMD.  The query map is applied to Q, the F key maps to K; the
+// features go to the fp32 feature workspace.  Workgroup x owns the 32-token tiles x, x + gridDim.x, ..
+// of both tensors, the key tiles first; its waves take them one at a time from a counter in LDS: of
+// three waves that share a SIMD the oldest is served first, so waves with equal shares of the tiles
+// finish far apart and the SIMD runs its last tiles one wave at a time.  A wave loads its next tile's
+// inputs while it computes the current one.
+// `split` (shared weights only): workgroup (x, y) applies map y alone.  The other form keeps all maps
+// in LDS and reads K once; with few tiles that leaves most waves without any, see forward_t.
+template <int D, int F, int WAVES, int DPH>
+__global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
+                                                        const unsigned char* __restrict__ wpk,
+                                                        int heads_w, int split, float* __restrict__ feat) {
   using SM = PhiSmem<D>;
   constexpr int NRB = D / 32, NKS = D / 16;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x % kWave, wave = wave_index();
   const int r = lane % 32, gl = lane / 32;
-  const TileMap tm = make_tile_map(g, heads_w);
+  TileMap tm = make_tile_map(g, heads_w);
   const int hw = heads_w == 1 ? 0 : blockIdx.y;
-  for (int m = 0; m < NMAPS; ++m)  // packed blocks are ordered [map][head]
-    load_weights<D, false, WAVES * 64>(smem + m * SM::kMap,
-                           wpk + (static_cast<int64_t>(map0 + m) * heads_w + hw) * Packed<D>::kBytes);
-  __syncthreads();
-  int a_off[NKS];
-  first_layer_offsets<D>(lane, a_off);
-  const int stride = gridDim.x * WAVES;
-  int tile = blockIdx.x * WAVES + wave;
+  const int64_t step = static_cast<int64_t>(heads_w) * Packed<D>::kBytes;  // packed blocks are ordered [map][head]
+  const int mbase = split ? blockIdx.y : 0;  // the map at the start of LDS
+  int* counter = reinterpret_cast<int*>(smem + (split ? 1 : 1 + F) * SM::kMap);
+  if (threadIdx.x == 0) *counter = WAVES;
+  // the list: entries 0 .. nk-1 are this workgroup's key tiles, nk .. nk+nq-1 its query tiles
+  const int own = (tm.total - static_cast<int>(blockIdx.x) + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+  const int nk = split && mbase == 0 ? 0 : own;
+  const int entries = nk + (split && mbase != 0 ? 0 : own);
+  int entry = wave;  // this wave's current one, then its next one
   int b = 0, h = 0, n0 = 0;
   // The tile's inputs live in xb only: the next tile's loads are issued into xb as soon as the
   // last first-layer MFMA of the current tile has read it (one and a half stages before the end).
   // The kernel is kept lean in registers (168) so that three waves share a SIMD.
   u32x4 xb[NKS];
-  if (tile < tm.total) {
-    tm.decode(tile, b, h, n0);
-    load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
-  }
+  auto fetch = [&]() {
+    const bool is_k = entry < nk;
+    tm.decode(blockIdx.x + (is_k ? entry : entry - nk) * gridDim.x, b, h, n0);
+    load_x<D>(is_k ? K : Q, b, h, n0 + r, g.N, gl, xb);
+  };
+  if (entry < entries) fetch();
+  if (split)
+    load_weights<D, false, WAVES * 64>(smem, wpk + mbase * step);
+  else
+    load_weights<D, false, WAVES * 64, 1 + F>(smem, wpk + static_cast<int64_t>(hw) * Packed<D>::kBytes, step);
+  __syncthreads();
+  int a_off[NKS];
+  first_layer_offsets<D>(lane, a_off);
   // features of the last finished map, not yet stored: accumulator register i of the second layer
   // is feature d_row(i, gl) = 8 (i/4) + 4 gl + i%4; the registers with a feature below d_phi on
   // either lane half are kept
@@ -249,6 +271,7 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
     }
     pend_ptr = nullptr;
   };
+  const int w2_lane = (gl * 16 + r % 16) * 16;  // rows 16 .. 31 of the second layer's product repeat, and are not used
   // the first layer accumulates on top of its bias: the lane's 16 entries of a 32-row block
   auto bias_acc = [&](const unsigned char* wmap, int rb) {
     f32x16 z;
@@ -263,12 +286,13 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
     }
     return z;
   };
-  for (; tile < tm.total; tile += stride) {
+  while (entry < entries) {
     const int n = n0 + r;
     const bool live = n < g.N;
     const int64_t th = g.th(b, h, live ? n : 0);
-    const bool more_tiles = tile + stride < tm.total;
-    if (more_tiles) tm.decode(tile + stride, b, h, n0);  // b, h, n0 now name the next tile
+    const int m0 = split ? mbase : (entry < nk ? 1 : 0), m1 = split ? mbase + 1 : (entry < nk ? 1 + F : 1);
+    int ticket = 0;
+    if (lane == 0) ticket = atomicAdd(counter, 1);  // read where the next tile's loads start
     // Software pipeline over 32-row blocks of the hidden layer (block t = m * NRB + rb): while the
     // vector ALU evaluates GELU on block t, the matrix pipe works on block t + 1, two MFMAs
     // between quarters of the vector work, their LDS operands read one quarter ahead.  Blocks
@@ -279,22 +303,23 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
     f32x16 hb[2];
     constexpr int kPer = NKS / 4;  // first-layer MFMAs per slice
     u32x4 an[kPer];                // their A operands, read one slice ahead
+    const unsigned char* w0 = smem + (m0 - mbase) * SM::kMap;
     {
       u32x4 a0[NKS];
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) a0[ks] = *reinterpret_cast<const u32x4*>(smem + a_off[ks]);
-      hb[0] = bias_acc(smem, 0);
+      for (int ks = 0; ks < NKS; ++ks) a0[ks] = *reinterpret_cast<const u32x4*>(w0 + a_off[ks]);
+      hb[0] = bias_acc(w0, 0);
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) hb[0] = mfma32(a0[ks], xb[ks], hb[0]);
 #pragma unroll
       for (int t = 0; t < kPer; ++t)
-        an[t] = *reinterpret_cast<const u32x4*>(smem + (1 % NRB) * 32 * SM::kRow + a_off[t]);
+        an[t] = *reinterpret_cast<const u32x4*>(w0 + (1 % NRB) * 32 * SM::kRow + a_off[t]);
     }
     flush();
 #pragma unroll 1
-    for (int m = 0; m < nmaps; ++m) {  // nmaps == NMAPS, passed at run time so this stays a loop
-      const unsigned char* wm = smem + m * SM::kMap;
-      const bool last_map = m + 1 == nmaps;
+    for (int m = m0; m < m1; ++m) {
+      const unsigned char* wm = smem + (m - mbase) * SM::kMap;
+      const bool last_map = m + 1 == m1;
       f32x16 u;
 #pragma unroll
       for (int i = 0; i < 16; ++i) u[i] = 0.0f;
@@ -308,8 +333,8 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
         f32x16& cur = hb[rb % 2];
         f32x16& nxt = hb[(rb + 1) % 2];
         nxt = bias_acc(w1, (rb + 1) % NRB);
-        const u32x4 a20 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + ((2 * rb) * 64 + lane) * 16);
-        const u32x4 a21 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + ((2 * rb + 1) * 64 + lane) * 16);
+        const u32x4 a20 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (2 * rb) * 512 + w2_lane);
+        const u32x4 a21 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (2 * rb + 1) * 512 + w2_lane);
         u32x4 gb[2];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -329,7 +354,10 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
           }
           if (j == 3) u = mfma32_f16(a20, gb[0], u);
           // the next tile's inputs: xb is free once the last first-layer MFMA has been issued
-          if (last_map && rb == NRB - 2 && j == 3 && more_tiles) load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
+          if (last_map && rb == NRB - 2 && j == 3) {
+            entry = __builtin_amdgcn_readfirstlane(ticket);
+            if (entry < entries) fetch();
+          }
           const float in[4] = {cur[4 * j], cur[4 * j + 1], cur[4 * j + 2], cur[4 * j + 3]};
           __builtin_amdgcn_sched_barrier(0);
           uint32_t out[2];
@@ -349,23 +377,11 @@ __device__ __forceinline__ void phi_fwd_body(const Geom& g, const View& X,
         const float* b2 = reinterpret_cast<const float*>(wm + SM::kW1 + SM::kW2 + D * 4) + 4 * gl;
 #pragma unroll
         for (int i = 0; i < NU; ++i) pend[i] = fmaxf(u[i] + b2[8 * (i / 4) + i % 4], 0.0f);
-        pend_ptr = live ? feat + g.fidx(th, (map0 + m) * DPH + 4 * gl) : nullptr;
+        pend_ptr = live ? feat + g.fidx(th, m * DPH + 4 * gl) : nullptr;
       }
     }
   }
   flush();
-}
-
-// The query map, then the F key maps, in one launch: a workgroup that has finished its share of
-// the query tiles swaps the weights in LDS and goes on with the key tiles, so the launch has no
-// boundary in between (no drain of the grid, no second cold start).  `nk` is F at run time.
-template <int D, int F, int WAVES, int DPH>
-__global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
-                                                        const unsigned char* __restrict__ wpk,
-                                                        int heads_w, int nk, float* __restrict__ feat) {
-  phi_fwd_body<D, 1, WAVES, DPH>(g, Q, wpk, heads_w, 0, 1, feat);
-  __syncthreads();  // every wave is done with the query map's weights
-  phi_fwd_body<D, F, WAVES, DPH>(g, K, wpk, heads_w, 1, nk, feat);
 }
 
 // ---- backward -----------------------------------------------------------------------------------
@@ -621,7 +637,8 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
   }
 }
 
-// dQ through the query map, then dK through the F key maps, in one launch (see k_phi_fwd)
+// dQ through the query map, then dK through the F key maps, in one launch: a workgroup that has finished its share of
+// the dQ tiles swaps the weights in LDS and goes on, without draining the grid in between
 template <int D, int F, int WAVES, int DPH>
 __global__ __launch_bounds__(WAVES * 64) void k_phi_bwd(Geom g, View Q, View K,
                                                         const unsigned char* __restrict__ wpk,
@@ -964,16 +981,22 @@ dim3 phi_grid(const hla_handle* hd, int waves) {
 // in the backward one
 constexpr int kWavesF = 12, kWavesB = 8;
 
-// F key maps of DPH features each, after the query map
+// F key maps of DPH features each, after the query map.  With shared weights and fewer than
+// kSplitTiles tiles a workgroup applies one map only (the 1 + F maps' workgroups side by side, K read
+// F times): otherwise a tile of K is three maps in a row on one wave while most of the waves have none.
+constexpr int kSplitTiles = 3072;  // tiles at which every wave of 256 workgroups has one of K
+
 template <int D, int F, int DPH>
 hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
   using SM = PhiSmem<D>;
   Geom g = hd->g;
   const unsigned char* wpk = static_cast<const unsigned char*>(hd->path_ws) + hd->w_packed_off;
-  const dim3 grid = phi_grid(hd, kWavesF);
-  HLA_TRY(launch(hd, "mfma_phi_forward", k_phi_fwd<D, F, kWavesF, DPH>, grid, dim3(kWavesF * 64),
-                 SM::total(F, kWavesF), a.stream, g, a.Q, a.K, wpk, hd->phi.heads_w, F, hd->feat));
-  return HLA_OK;
+  const int64_t tiles = static_cast<int64_t>((g.N + 31) / 32) * g.B * g.H;
+  const int split = hd->phi.heads_w == 1 && tiles < kSplitTiles;
+  dim3 grid = phi_grid(hd, kWavesF);
+  if (split) grid = dim3(static_cast<unsigned>(std::min<int64_t>(256 / (1 + F), tiles)), 1 + F, 1);
+  return launch(hd, "mfma_phi_forward", k_phi_fwd<D, F, kWavesF, DPH>, grid, dim3(kWavesF * 64),
+                SM::total(split ? 1 : 1 + F, kWavesF), a.stream, g, a.Q, a.K, wpk, hd->phi.heads_w, split, hd->feat);
 }
 
 template <int D, int F, int DPH>
@@ -1017,7 +1040,7 @@ hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
 
 template <int D, int F, int DPH>
 hla_status prepare_t() {
-  HLA_TRY(allow_lds(&k_phi_fwd<D, F, kWavesF, DPH>, PhiSmem<D>::total(F, kWavesF)));
+  HLA_TRY(allow_lds(&k_phi_fwd<D, F, kWavesF, DPH>, PhiSmem<D>::total(1 + F, kWavesF)));
   HLA_TRY(allow_lds(&k_phi_bwd<D, F, kWavesB, DPH>, PhiSmem<D, true>::total(F, kWavesB)));
   return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, kWavesW / (D / 32) * WgSmem<D>::kBufs * WgSmem<D>::kBuf);
 }
