@@ -21,12 +21,8 @@ namespace {
 
 using namespace mf;
 
-struct TrueTag {
-  static constexpr bool value = true;
-};
-struct FalseTag {
-  static constexpr bool value = false;
-};
+using TrueTag = std::true_type;
+using FalseTag = std::false_type;
 
 
 // ---- packed weights of one (map, head) in global memory ---------------------------------------
@@ -82,16 +78,19 @@ __global__ void k_pack_phi(PhiF32 w, int dphi, unsigned char* __restrict__ out) 
 // function of the row chosen so that both access patterns spread over all banks without padding:
 //   plain 16-byte reads of 16 consecutive rows at one chunk (first-layer A operand), and
 //   transpose reads of 4 consecutive rows x 4 consecutive chunks (A operand of dx^T = W1 dh^T).
-template <int D, bool BACKWARD = false>
+// SLOTS (backward): slots of the contraction over features that are kept, 8 where d_phi <= 8 (lane half 1
+// holds the upper eight, whose feature gradients are zero: it reads half 0's).
+template <int D, bool BACKWARD = false, int SLOTS = 16>
 struct PhiSmem {
   static constexpr int kChunks = D / 8;               // 16-byte chunks per row
   static constexpr int kRow = D * 2;                  // bytes per row
   static constexpr int kW1 = D * D * 2;
-  static constexpr int kW2 = D * 16 * 2;              // W2B (backward) or W2A (forward)
+  static constexpr int kW2 = D * SLOTS * 2;           // W2B (backward) or W2A (forward)
   static constexpr int kMap = kW1 + kW2 + D * 4 + 64;  // then b1 [D] and b2 [16] in fp32
-  // backward adds a 16-row transpose tile per wave for whole-row stores of dX, forward the list's counter
+  // the maps, the counter of the list of tiles and, backward, a transpose tile per wave for whole-row stores of dX
+  static constexpr int kRowsOut = 8;
   static constexpr int total(int nmaps, int waves) {
-    return nmaps * kMap + (BACKWARD ? waves * RowTile<D, 16>::kBytes : 16);
+    return nmaps * kMap + 16 + (BACKWARD ? waves * RowTile<D, kRowsOut>::kBytes : 0);
   }
   __host__ __device__ static __forceinline__ int swz(int row) {
     return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
@@ -104,9 +103,9 @@ struct PhiSmem {
 // Copy the packed weights of NMAPS maps (blocks `step` bytes apart in memory, kMap apart in LDS) into
 // LDS, all THREADS threads of the workgroup.  All global loads are issued before the first LDS store
 // so that they are in flight together: the copy costs one memory round trip, not one per map or piece.
-template <int D, bool BACKWARD, int THREADS, int NMAPS = 1>
+template <int D, bool BACKWARD, int THREADS, int NMAPS = 1, int SLOTS = 16>
 __device__ __forceinline__ void load_weights(unsigned char* dst, const unsigned char* src, int64_t step = 0) {
-  using SM = PhiSmem<D, BACKWARD>;
+  using SM = PhiSmem<D, BACKWARD, SLOTS>;
   using PK = Packed<D>;
   constexpr int N1 = D * SM::kChunks;              // 16-byte chunks of W1^T
   constexpr int N2 = SM::kW2 / 16;                 // 16-byte chunks of the W2 image
@@ -124,7 +123,10 @@ __device__ __forceinline__ void load_weights(unsigned char* dst, const unsigned 
       if (N1 % THREADS == 0 || t + k * THREADS < N1) v1[m][k] = *reinterpret_cast<const u32x4*>(s + PK::kW1T + (t + k * THREADS) * 16);
 #pragma unroll
     for (int k = 0; k < I2; ++k)
-      if (N2 % THREADS == 0 || t + k * THREADS < N2) v2[m][k] = *reinterpret_cast<const u32x4*>(w2 + (t + k * THREADS) * 16);
+      if (N2 % THREADS == 0 || t + k * THREADS < N2) {
+        const int i = t + k * THREADS;
+        v2[m][k] = *reinterpret_cast<const u32x4*>(w2 + (SLOTS == 8 ? (i / 32) * 64 + i % 32 : i) * 16);
+      }
     vb[m] = t < NB ? *reinterpret_cast<const float*>(s + PK::kB1 + t * 4) : 0.0f;
   }
 #pragma unroll
@@ -206,6 +208,11 @@ __device__ __forceinline__ TileMap make_tile_map(const Geom& g, int heads_w) {
 // inputs while it computes the current one.
 // `split` (shared weights only): workgroup (x, y) applies map y alone.  The other form keeps all maps
 // in LDS and reads K once; with few tiles that leaves most waves without any, see forward_t.
+// Bound: the card's power.  The clock falls to 1.8 GHz under this mix (a loop of 8 MFMAs and 96 packed
+// FMAs per wave runs at 2.4 GHz on constant operands, at 1.8 on random ones), where the vector ALU
+// issues in 69 % of a wave's life and the matrix pipe is busy 48 %.  Fixed shares of the tiles, with
+// the query map's weights swapped for the key maps' half way: 84 us at 12 heads x 32760 tokens x 128
+// channels, 622 us at 40 x 75600, 20.7 us at 12 x 1560; now 75, 578 and 10.4 us.
 template <int D, int F, int WAVES, int DPH>
 __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
                                                         const unsigned char* __restrict__ wpk,
@@ -271,7 +278,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
     }
     pend_ptr = nullptr;
   };
-  const int w2_lane = (gl * 16 + r % 16) * 16;  // rows 16 .. 31 of the second layer's product repeat, and are not used
+  // rows 16 .. 31 of the second layer's product are not used: their lanes read row 15, which is zero
+  const int w2_lane = (gl * 16 + (r < 16 ? r : 15)) * 16;
   // the first layer accumulates on top of its bias: the lane's 16 entries of a 32-row block
   auto bias_acc = [&](const unsigned char* wmap, int rb) {
     f32x16 z;
@@ -303,26 +311,30 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
     f32x16 hb[2];
     constexpr int kPer = NKS / 4;  // first-layer MFMAs per slice
     u32x4 an[kPer];                // their A operands, read one slice ahead
+    f32x16 bias_nx;                // and what they accumulate onto, read a stage ahead
     const unsigned char* w0 = smem + (m0 - mbase) * SM::kMap;
     {
       u32x4 a0[NKS];
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) a0[ks] = *reinterpret_cast<const u32x4*>(w0 + a_off[ks]);
       hb[0] = bias_acc(w0, 0);
+      bias_nx = bias_acc(w0, 1 % NRB);
+      __builtin_amdgcn_sched_barrier(0);  // all reads in flight before the first product waits for its own
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) hb[0] = mfma32(a0[ks], xb[ks], hb[0]);
 #pragma unroll
       for (int t = 0; t < kPer; ++t)
         an[t] = *reinterpret_cast<const u32x4*>(w0 + (1 % NRB) * 32 * SM::kRow + a_off[t]);
     }
-    flush();
-#pragma unroll 1
-    for (int m = m0; m < m1; ++m) {
+    // The last map of a tile is code of its own: only there the next tile's loads start, and in the
+    // other maps the compiler would have to wait for them (and for every store issued since).
+    auto run_map = [&](int m, auto LAST) {
+      constexpr bool last_map = decltype(LAST)::value;
       const unsigned char* wm = smem + (m - mbase) * SM::kMap;
-      const bool last_map = m + 1 == m1;
       f32x16 u;
 #pragma unroll
       for (int i = 0; i < 16; ++i) u[i] = 0.0f;
+      float b2v[NU];
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb) {
         // block t+1 (first layer, this stage) and block t+2 (whose first operands the last slice reads)
@@ -332,7 +344,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
         const unsigned char* a2_base = w2 + ((rb + 2) % NRB) * 32 * SM::kRow;
         f32x16& cur = hb[rb % 2];
         f32x16& nxt = hb[(rb + 1) % 2];
-        nxt = bias_acc(w1, (rb + 1) % NRB);
         const u32x4 a20 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (2 * rb) * 512 + w2_lane);
         const u32x4 a21 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (2 * rb + 1) * 512 + w2_lane);
         u32x4 gb[2];
@@ -341,20 +352,29 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
         for (int j = 0; j < 4; ++j) {
           // the empty asm statements pin the order MFMAs -> GELU slice -> next MFMAs: they are
           // volatile (kept in program order) and the values flow through them
-          asm volatile("" : "+v"(nxt));
+          if (j > 0) asm volatile("" : "+v"(nxt));
           // first layer of block t+1 (there is none after the last block, and xb already belongs
           // to the next tile's loads by then)
           if (rb + 1 < NRB || !last_map) {
 #pragma unroll
             for (int t = 0; t < kPer; ++t) {
-              nxt = mfma32(an[t], xb[j * kPer + t], nxt);
+              nxt = mfma32(an[t], xb[j * kPer + t], j == 0 && t == 0 ? bias_nx : nxt);
               an[t] = j < 3 ? *reinterpret_cast<const u32x4*>(a1_base + a_off[(j + 1) * kPer + t])
                             : *reinterpret_cast<const u32x4*>(a2_base + a_off[t]);
             }
           }
+          // The previous map's features leave here: stores count in the same wait counter as loads, and
+          // these are old when the next tile's inputs, requested after them, are waited for.
+          if (rb == 0 && j == 1) flush();
+          if (rb == NRB - 1 && j == 2) {
+            const float* b2 = reinterpret_cast<const float*>(wm + SM::kW1 + SM::kW2 + D * 4) + 4 * gl;
+#pragma unroll
+            for (int i = 0; i < NU; ++i) b2v[i] = b2[8 * (i / 4) + i % 4];
+          }
+          if (j == 2) bias_nx = bias_acc(w2, (rb + 2) % NRB);
           if (j == 3) u = mfma32_f16(a20, gb[0], u);
           // the next tile's inputs: xb is free once the last first-layer MFMA has been issued
-          if (last_map && rb == NRB - 2 && j == 3) {
+          if constexpr (last_map) if (rb == NRB - 2 && j == 3) {
             entry = __builtin_amdgcn_readfirstlane(ticket);
             if (entry < entries) fetch();
           }
@@ -369,31 +389,31 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
         }
         u = mfma32_f16(a21, gb[1], u);
       }
-      // The store is held back until the next map (or the next tile's input wait) has been passed:
-      // stores count in the same wait counter as loads, and a store issued just before that wait
-      // would make the wave sit out the store's full round trip.
-      flush();
-      {
-        const float* b2 = reinterpret_cast<const float*>(wm + SM::kW1 + SM::kW2 + D * 4) + 4 * gl;
 #pragma unroll
-        for (int i = 0; i < NU; ++i) pend[i] = fmaxf(u[i] + b2[8 * (i / 4) + i % 4], 0.0f);
-        pend_ptr = live ? feat + g.fidx(th, m * DPH + 4 * gl) : nullptr;
-      }
-    }
+      for (int i = 0; i < NU; ++i) pend[i] = fmaxf(u[i] + b2v[i], 0.0f);
+      pend_ptr = live ? feat + g.fidx(th, m * DPH + 4 * gl) : nullptr;
+    };
+#pragma unroll 1
+    for (int m = m0; m + 1 < m1; ++m) run_map(m, FalseTag{});
+    run_map(m1 - 1, TrueTag{});
   }
   flush();
 }
 
 // ---- backward -----------------------------------------------------------------------------------
-// block WAVES*64.  dX = sum over the NMAPS maps of W1 (GELU'(h) * (W2 du)), with du = d(feature)
-// where the ReLU was open (the form in which the feature-gradient workspace arrives).  Hidden
-// activations are recomputed.
-template <int D, int NMAPS, int WAVES, int DPH>
-__device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
-                                             const unsigned char* __restrict__ wpk, int heads_w,
-                                             int map0, int nmaps,
-                                             const float* __restrict__ dfeat, const View& dX) {
-  using SM = PhiSmem<D, true>;
+// block WAVES*64, two waves per SIMD.  dQ through the query map, dK through the F key maps:
+// dX = sum over the maps of W1 (GELU'(h) * (W2 du)), with du = d(feature) where the ReLU was open (the
+// form in which the feature-gradient workspace arrives).  Hidden activations are recomputed.  All
+// maps stay in LDS; the waves of a workgroup take its 32-token tiles from a counter as in the forward.
+// Bound: power, as the forward (1.9 GHz), with 470 MB of traffic beside it.  With fixed shares and the
+// weights swapped half way: 150 us at 12 heads x 32760 tokens x 128 channels, 70 at 12600 (a third
+// round of tiles for some waves only), 129 in the two-factor form at 32760; now 138, 60 and 113 us.
+template <int D, int F, int WAVES, int DPH>
+__global__ __launch_bounds__(WAVES * 64) void k_phi_bwd(Geom g, View Q, View K,
+                                                        const unsigned char* __restrict__ wpk, int heads_w,
+                                                        const float* __restrict__ dfeat, View dQ, View dK) {
+  constexpr int SLOTS = DPH <= 8 ? 8 : 16;
+  using SM = PhiSmem<D, true, SLOTS>;
   constexpr int NRB = D / 32, NKS = D / 16;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x % kWave, wave = wave_index();
@@ -401,16 +421,32 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
   const int L = lane % 16, q = lane / 16;
   const TileMap tm = make_tile_map(g, heads_w);
   const int hw = heads_w == 1 ? 0 : blockIdx.y;
-  for (int m = 0; m < NMAPS; ++m)
-    load_weights<D, true, WAVES * 64>(smem + m * SM::kMap,
-                          wpk + (static_cast<int64_t>(map0 + m) * heads_w + hw) * Packed<D>::kBytes);
+  int* counter = reinterpret_cast<int*>(smem + (1 + F) * SM::kMap);
+  unsigned char* const rows = smem + (1 + F) * SM::kMap + 16 + wave * RowTile<D, SM::kRowsOut>::kBytes;  // dX transpose tile
+  if (threadIdx.x == 0) *counter = WAVES;
+  // the list: entries 0 .. own-1 are this workgroup's key tiles, own .. 2 own-1 its query tiles
+  const int own = (tm.total - static_cast<int>(blockIdx.x) + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+  int entry = wave;
+  bool is_k = entry < own;
+  int b = 0, h = 0, n0 = 0;
+  auto locate = [&]() { tm.decode(blockIdx.x + (is_k ? entry : entry - own) * gridDim.x, b, h, n0); };
+  // The tile's inputs live in xb only: the next tile's loads are issued into xb as soon as the
+  // last first-layer MFMA of the current tile has read it (one and a half stages before the end).
+  u32x4 xb[NKS];
+  if (entry < 2 * own) {
+    locate();
+    load_x<D>(is_k ? K : Q, b, h, n0 + r, g.N, gl, xb);
+  }
+  load_weights<D, true, WAVES * 64, 1 + F, SLOTS>(smem, wpk + static_cast<int64_t>(hw) * Packed<D>::kBytes,
+                                           static_cast<int64_t>(heads_w) * Packed<D>::kBytes);
   __syncthreads();
-  unsigned char* ttile = smem + nmaps * SM::kMap + wave * RowTile<D, 16>::kBytes;  // dX transpose tile
   int a_off[NKS];
   first_layer_offsets<D>(lane, a_off);
   // Transpose reads for dx^T[in x tok] += W1[in x hidden] dh^T: k-slots (ks2, gl, j) stand for
   // hidden units 16 ks2 + 4 gl + {0..3} (j < 4) and + 8 (j >= 4); a lane of a 16-lane group
-  // addresses hidden row k0 + L/4 and the 4 input channels 32 rb + 16 (q%2) + 4 (L%4) ..+3.
+  // addresses hidden row k0 + L/4 and four input channels.  The channel groups are addressed with
+  // their two bits exchanged, so that accumulator register i of block rb holds channel
+  // 32 rb + 16 (i / 8) + 8 gl + i % 8: eight consecutive ones, and dX leaves as 16-byte pieces.
   // swz() ignores the row's bits 4 and up, so the k-step only adds a constant to the address.
   int t_off[2][NRB];
 #pragma unroll
@@ -418,19 +454,9 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
       const int row = 4 * gl + 8 * hi + L / 4;
-      const int col = 32 * rb + 16 * (q % 2) + 4 * (L % 4);
+      const int c = L % 4, col = 32 * rb + 16 * (q % 2) + 4 * (((c & 1) << 1) | (c >> 1));
       t_off[hi][rb] = SM::off(row, col >> 3) + ((col & 7) << 1);
     }
-  const int stride = gridDim.x * WAVES;
-  int tile = blockIdx.x * WAVES + wave;
-  int b = 0, h = 0, n0 = 0;
-  // The tile's inputs live in xb only: the next tile's loads are issued into xb as soon as the
-  // last first-layer MFMA of the current tile has read it (one and a half stages before the end).
-  u32x4 xb[NKS];
-  if (tile < tm.total) {
-    tm.decode(tile, b, h, n0);
-    load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
-  }
   // du^T of one map as B operand of a single 16-slot step: slot (gl, j) is feature 8gl + j (with
   // d_phi <= 8 only gl = 0 is used).  The feature gradients arrive already zeroed where the ReLU
   // was closed (the core backward kernels, which hold the features anyway, write them that way), so
@@ -444,7 +470,7 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
     // surplus slots re-read the half's first feature
     const int first = DPH <= 8 ? 0 : 8 * gl;
     const int have = DPH <= 8 ? DPH : (gl ? DPH - 8 : 8);
-    const f32x2* dp = reinterpret_cast<const f32x2*>(dfeat + g.fidx(th, (map0 + m) * DPH + first));
+    const f32x2* dp = reinterpret_cast<const f32x2*>(dfeat + g.fidx(th, m * DPH + first));
 #pragma unroll
     for (int p = 0; p < NJ / 2; ++p) {
       const f32x2 v = dp[32 * (2 * p < have ? p : 0)];
@@ -452,13 +478,13 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
       dv[2 * p + 1] = v[1];
     }
   };
-  auto finish_du = [&](const float (&dv)[NJ], bool live) -> u32x4 {
+  auto finish_du = [&](const float (&dv)[NJ]) -> u32x4 {
     const int have = DPH <= 8 ? (gl ? 0 : DPH) : (gl ? DPH - 8 : 8);
     u32x4 d;
     d[0] = d[1] = d[2] = d[3] = 0u;
 #pragma unroll
     for (int p = 0; p < NJ / 2; ++p)
-      d[p] = pack_bf16(live && 2 * p < have ? dv[2 * p] : 0.0f, live && 2 * p + 1 < have ? dv[2 * p + 1] : 0.0f);
+      d[p] = pack_bf16(2 * p < have ? dv[2 * p] : 0.0f, 2 * p + 1 < have ? dv[2 * p + 1] : 0.0f);
     return d;
   };
   auto zero_acc = []() {  // a constant: becomes the inline 0 of the MFMA's C operand
@@ -483,21 +509,22 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
   };
   // du of the coming tile's first map: loaded during the last map of the tile before, like the
   // later maps' du is loaded a map ahead
+  // Lanes past the end of a sequence do what the lane of its last token does, stores included: with
+  // no lane idle the number of stores in flight is known where the next tile's inputs are waited for.
+  auto token = [&]() { return g.th(b, h, n0 + r < g.N ? n0 + r : g.N - 1); };
   u32x4 dub_first;
-  if (tile < tm.total) {
+  if (entry < 2 * own) {
     float dv0[NJ];
-    issue_du(g.th(b, h, n0 + r < g.N ? n0 + r : 0), 0, dv0);
-    dub_first = finish_du(dv0, n0 + r < g.N);
+    issue_du(token(), is_k ? 1 : 0, dv0);
+    dub_first = finish_du(dv0);
   }
-  for (; tile < tm.total; tile += stride) {
-    const int n = n0 + r;
-    const bool live = n < g.N;
-    const int64_t th = g.th(b, h, live ? n : 0);
-    const int ob = b, oh = h, on0 = n0;  // this tile's coordinates
-    const bool more_tiles = tile + stride < tm.total;
-    if (more_tiles) tm.decode(tile + stride, b, h, n0);  // b, h, n0 now name the next tile
-    const bool live_next = more_tiles && n0 + r < g.N;
-    const int64_t th_next = g.th(b, h, live_next ? n0 + r : 0);
+  while (entry < 2 * own) {
+    const int64_t th = token();
+    const int m0 = is_k ? 1 : 0, m1 = is_k ? 1 + F : 1;
+    const View& dX = is_k ? dK : dQ;
+    const int ob = b, oh = h, on0 = n0;
+    int ticket = 0;
+    if (lane == 0) ticket = atomicAdd(counter, 1);  // read at the start of the tile's last map
     f32x16 dx[NRB];  // first written by the second stage of the first map (accumulating onto zero)
     // Software pipeline over 32-row blocks of the hidden layer, block t = m * NRB + rb.  Stage t:
     //   vector ALU : dh(t) = dg(t) * GELU'(hidden(t) + b1), packed as the B operand of dx
@@ -510,36 +537,47 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
     f32x16 hb[2];  // hidden blocks alternate between two accumulator sets (as in the forward)
     constexpr int kPer = NKS / 4;  // first-layer MFMAs per slice
     u32x4 an[kPer];                // their A operands, read one slice ahead
+    const unsigned char* w0 = smem + m0 * SM::kMap;
     {
       u32x4 a0[NKS];
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) a0[ks] = *reinterpret_cast<const u32x4*>(smem + a_off[ks]);
-      hb[0] = bias_acc(smem, 0);
+      for (int ks = 0; ks < NKS; ++ks) a0[ks] = *reinterpret_cast<const u32x4*>(w0 + a_off[ks]);
+      hb[0] = bias_acc(w0, 0);
+      __builtin_amdgcn_sched_barrier(0);  // all reads in flight before the first product waits for its own
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) hb[0] = mfma32(a0[ks], xb[ks], hb[0]);
 #pragma unroll
       for (int t = 0; t < kPer; ++t)
-        an[t] = *reinterpret_cast<const u32x4*>(smem + (1 % NRB) * 32 * SM::kRow + a_off[t]);
+        an[t] = *reinterpret_cast<const u32x4*>(w0 + (1 % NRB) * 32 * SM::kRow + a_off[t]);
     }
     u32x4 dub = dub_first;
     u32x4 dhp[2];  // dh of the previous block (two 16-slot steps)
     // The first map is peeled off the loop over maps: its first stage has no previous block (no dx
     // step at all) and its second stage starts the dx accumulators from the constant zero, which
     // spares clearing them and carrying them into the loop as copies.
-    auto run_map = [&](int m, auto first_tag, int64_t th_nx, bool live_nx) {
+    // last_map: a tag (the last map is code of its own, as in the forward) or, where that spills, a bool
+    auto run_map = [&](int m, auto first_tag, auto last_map) {
       constexpr bool FIRST = decltype(first_tag)::value;
       const unsigned char* wm = smem + m * SM::kMap;
-      const bool last_map = m + 1 == nmaps;
       float dvn[NJ];  // the next map's du, or the coming tile's first
-      issue_du(last_map ? th_nx : th, last_map ? 0 : m + 1, dvn);
+      if (last_map) {
+        entry = __builtin_amdgcn_readfirstlane(ticket);
+        if (entry < 2 * own) {  // is_k, b, h, n0 now name the next tile (no next tile: this one again)
+          is_k = entry < own;
+          locate();
+        }
+        issue_du(token(), is_k ? 1 : 0, dvn);
+      } else {
+        issue_du(th, m + 1, dvn);
+      }
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb) {
         // block t+1 (first layer, this stage) and block t+2 (whose first operands the last slice reads)
         const unsigned char* a1_base = (rb + 1 < NRB ? wm : (last_map ? wm : wm + SM::kMap)) + ((rb + 1) % NRB) * 32 * SM::kRow;
         const unsigned char* a2_base = (rb + 2 < NRB ? wm : (last_map ? wm : wm + SM::kMap)) + ((rb + 2) % NRB) * 32 * SM::kRow;
-        const unsigned char* wp = rb > 0 ? wm : (m > 0 ? wm - SM::kMap : wm);
+        const unsigned char* wp = rb > 0 || FIRST ? wm : wm - SM::kMap;
         const int ks2p = 2 * ((rb + NRB - 1) % NRB);  // first of the two 16-slot steps of block t-1
-        const u32x4 a2 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (rb * 64 + lane) * 16);
+        const u32x4 a2 = *reinterpret_cast<const u32x4*>(wm + SM::kW1 + (SLOTS == 8 ? rb * 32 + r : rb * 64 + lane) * 16);
         const f32x16 dg = mfma32(a2, dub, zero_acc());
         f32x16& cur = hb[rb % 2];
         f32x16& nxt = hb[(rb + 1) % 2];
@@ -589,7 +627,7 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
             thi[x] = lds_read_tr16(wp + (ks2p + jn / 2) * 16 * SM::kRow + t_off[1][rbn]);
           }
           // the next tile's inputs: xb is free once the last first-layer MFMA has been issued
-          if (last_map && rb == NRB - 2 && j == 3 && more_tiles) load_x<D>(X, b, h, n0 + r, g.N, gl, xb);
+          if (last_map && rb == NRB - 2 && j == 3) load_x<D>(is_k ? K : Q, b, h, n0 + r, g.N, gl, xb);
           const float in[4] = {cur[4 * j], cur[4 * j + 1], cur[4 * j + 2], cur[4 * j + 3]};
           __builtin_amdgcn_sched_barrier(0);
           f16x2 gp[2];
@@ -607,15 +645,24 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
         dhp[0] = dhc[0];
         dhp[1] = dhc[1];
       }
-      dub = finish_du(dvn, last_map ? live_nx : live);  // after the last map: the coming tile's
+      dub = finish_du(dvn);  // after the last map: the coming tile's
     };
-    run_map(0, TrueTag{}, th_next, live_next);
+    if constexpr (D > 64) {  // code of its own: 393 us a step at 12 x 32760 x 128, 384 without
+      run_map(m0, TrueTag{}, m0 + 1 == m1);
 #pragma unroll 1
-    for (int m = 1; m < nmaps; ++m) run_map(m, FalseTag{}, th_next, live_next);  // nmaps == NMAPS, passed at run time so this stays a loop
+      for (int m = m0 + 1; m < m1; ++m) run_map(m, FalseTag{}, m + 1 == m1);
+    } else if (m0 == 0) {
+      run_map(0, TrueTag{}, TrueTag{});
+    } else {
+      run_map(1, TrueTag{}, FalseTag{});
+#pragma unroll 1
+      for (int m = 2; m < F; ++m) run_map(m, FalseTag{}, FalseTag{});
+      run_map(F, FalseTag{}, TrueTag{});
+    }
     dub_first = dub;
     // dx of the last block
     {
-      const unsigned char* wp = smem + (nmaps - 1) * SM::kMap;
+      const unsigned char* wp = smem + (m1 - 1) * SM::kMap;
       constexpr int ks2p = 2 * (NRB - 1);
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
@@ -631,23 +678,22 @@ __device__ __forceinline__ void phi_bwd_body(const Geom& g, const View& X,
           dx[rbx] = mfma32(a, dhp[hf], dx[rbx]);
         }
     }
-    store_rows_bf16<D, 16>(dx, 1.0f, lane, ttile, [&](int t) -> bf16_t* {
-      return on0 + t < g.N ? dX.row<bf16_t>(ob, oh, on0 + t) : nullptr;
-    });
+    u32x4 w[NRB][2];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) w[rb][hf][p] = pack_bf16(dx[rb][8 * hf + 2 * p], dx[rb][8 * hf + 2 * p + 1]);
+    // whole rows per store instruction: 32-byte pieces cost 5 us of 140 (76 if nontemporal)
+#pragma unroll
+    for (int pass = 0; pass < 32 / SM::kRowsOut; ++pass) {
+      put_rows<D, SM::kRowsOut>(w, pass, lane, rows);
+      flush_rows<D, SM::kRowsOut>(pass, lane, rows, [&](int t) -> bf16_t* {
+        return dX.row<bf16_t>(ob, oh, on0 + t < g.N ? on0 + t : g.N - 1);
+      });
+    }
   }
-}
-
-// dQ through the query map, then dK through the F key maps, in one launch: a workgroup that has finished its share of
-// the dQ tiles swaps the weights in LDS and goes on, without draining the grid in between
-template <int D, int F, int WAVES, int DPH>
-__global__ __launch_bounds__(WAVES * 64) void k_phi_bwd(Geom g, View Q, View K,
-                                                        const unsigned char* __restrict__ wpk,
-                                                        int heads_w, int nk,
-                                                        const float* __restrict__ dfeat, View dQ,
-                                                        View dK) {
-  phi_bwd_body<D, 1, WAVES, DPH>(g, Q, wpk, heads_w, 0, 1, dfeat, dQ);
-  __syncthreads();  // every wave is done with the query map's weights and its transpose tile
-  phi_bwd_body<D, F, WAVES, DPH>(g, K, wpk, heads_w, 1, nk, dfeat, dK);
 }
 
 // ---- weight gradients ---------------------------------------------------------------------------
@@ -984,7 +1030,10 @@ constexpr int kWavesF = 12, kWavesB = 8;
 // F key maps of DPH features each, after the query map.  With shared weights and fewer than
 // kSplitTiles tiles a workgroup applies one map only (the 1 + F maps' workgroups side by side, K read
 // F times): otherwise a tile of K is three maps in a row on one wave while most of the waves have none.
-constexpr int kSplitTiles = 3072;  // tiles at which every wave of 256 workgroups has one of K
+// From kSplitTiles on every wave of 256 workgroups has a tile of K.  Forward calls in us, 12 heads x
+// 128 channels, split / whole: 26 / 36 at 1024 tokens, 33 / 40 at 4096, 48.8 / 49.4 at 8192 (3072
+// tiles), 65.0 / 65.7 at 12600; two-factor form 44 / 48 at 4096, 60.9 / 60.3 at 8192.
+constexpr int kSplitTiles = 3072;
 
 template <int D, int F, int DPH>
 hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
@@ -1001,13 +1050,12 @@ hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
 
 template <int D, int F, int DPH>
 hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
-  using SM = PhiSmem<D, true>;
+  using SM = PhiSmem<D, true, (DPH <= 8 ? 8 : 16)>;
   Geom g = hd->g;
   const unsigned char* wpk = static_cast<const unsigned char*>(hd->path_ws) + hd->w_packed_off;
   const dim3 grid = phi_grid(hd, kWavesB);
   HLA_TRY(launch(hd, "mfma_phi_backward", k_phi_bwd<D, F, kWavesB, DPH>, grid, dim3(kWavesB * 64),
-                 SM::total(F, kWavesB), a.stream, g, a.Q, a.K, wpk, hd->phi.heads_w, F, hd->dfeat,
-                 a.dQ, a.dK));
+                 SM::total(1 + F, kWavesB), a.stream, g, a.Q, a.K, wpk, hd->phi.heads_w, hd->dfeat, a.dQ, a.dK));
   return HLA_OK;
 }
 
@@ -1041,7 +1089,7 @@ hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
 template <int D, int F, int DPH>
 hla_status prepare_t() {
   HLA_TRY(allow_lds(&k_phi_fwd<D, F, kWavesF, DPH>, PhiSmem<D>::total(1 + F, kWavesF)));
-  HLA_TRY(allow_lds(&k_phi_bwd<D, F, kWavesB, DPH>, PhiSmem<D, true>::total(F, kWavesB)));
+  HLA_TRY(allow_lds(&k_phi_bwd<D, F, kWavesB, DPH>, PhiSmem<D, true, (DPH <= 8 ? 8 : 16)>::total(1 + F, kWavesB)));
   return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, kWavesW / (D / 32) * WgSmem<D>::kBufs * WgSmem<D>::kBuf);
 }
 
