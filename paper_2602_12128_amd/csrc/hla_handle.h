@@ -83,7 +83,7 @@ struct hla_handle {
   bool vmod_wg_on = false;
   hla_vmod_weight_grads vmod_wg_out[2] = {};
   float* vmod_wg_partial = nullptr;  // [kVmodWgradParts][d d + d]
-  float* vmod_wg_rows = nullptr;     // three [max_th][d] arrays of per-token factors
+  float* vmod_wg_rows = nullptr;     // per-token factors: three [max_th][d] arrays, or what hla_mfma_vmod.hip keeps
 
   // token tables, one per role (the path's workspace plan names the roles it uses)
   hla_token_table tables[kTableRoles];

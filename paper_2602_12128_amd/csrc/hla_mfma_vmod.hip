@@ -46,7 +46,8 @@ struct VPacked {
   static constexpr int kB2 = kB1 + D * 4;         // fp32 [D]
   static constexpr int kGamma = kB2 + D * 4;      // fp32 [D]
   static constexpr int kBeta = kGamma + D * 4;    // fp32 [D]
-  static constexpr int kBytes = kBeta + D * 4;
+  static constexpr int kW2 = kBeta + D * 4;       // fp16 [D][D]: row = hidden unit, col = output channel; times 4
+  static constexpr int kBytes = kW2 + D * D * 2;
 };
 
 template <typename T>
@@ -56,10 +57,12 @@ __global__ void k_vmod_pack_mfma(const T* W1, const T* b1, const T* W2, const T*
   uint16_t* w1t = reinterpret_cast<uint16_t*>(out);
   uint16_t* w2t = w1t + d * d;
   float* vec = reinterpret_cast<float*>(w2t + d * d);
+  uint16_t* w2 = reinterpret_cast<uint16_t*>(vec + 4 * d);
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d * d; i += gridDim.x * blockDim.x) {
     const int row = i / d, col = i % d;  // row = output of the layer, col = its input
     w1t[i] = f32_to_bf16_bits(kHiddenScale * to_float(W1[col * d + row]));
     w2t[i] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(to_float(W2[col * d + row]) / kHiddenScale));
+    w2[i] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(to_float(W2[i]) / kHiddenScale));
     if (i < d) {
       vec[i] = kHiddenScale * to_float(b1[i]);
       vec[d + i] = to_float(b2[i]);
@@ -162,26 +165,17 @@ struct SavedTile {
   static constexpr int kBytes = kUhat + 2 * 256;
 };
 
-// Per-token factors of the maps' weight gradients, written by the backward kernel when they are
-// asked for: bf16 [token-heads][D] arrays per map m (nullptr: not wanted).  With them
-//   dW2 = G^T dU, db2 = sum dU;  dW1 = X^T dH, db1 = sum dH.
-// The LayerNorm's dgamma = sum over tokens of dm * u-hat and dbeta = sum of dm (dm: gradient w.r.t.
-// the map's output) need no arrays: the backward kernel adds them up per lane as it goes and
-// leaves one partial per workgroup in gb_part ([workgroup][dgamma | dbeta][D] floats).
+// What the backward kernel leaves of map m for the maps' weight gradients when they are asked for: the
+// gradient w.r.t. the second layer's output as the matrix cores see it (fp16 [token-heads][D], a token's
+// row scaled to unit norm) and the scale of each token.  The LayerNorm's dgamma = sum over tokens of
+// dm * u-hat and dbeta = sum of dm (dm: gradient w.r.t. the map's output) need no array: the kernel adds
+// them up per lane as it goes and leaves one partial per workgroup in gb_part
+// ([workgroup][dgamma | dbeta][D] floats).
 struct VmodFactors {
-  bf16_t* dU[2];   // gradient w.r.t. the second layer's output
-  bf16_t* dH[2];   // gradient w.r.t. the first layer's output
-  bf16_t* G[2];    // GELU(h)
+  uint16_t* t[2];
+  float* scale[2];
   float* gb_part;
 };
-
-// eight fp32 values -> a 16-byte piece of a bf16 row
-__device__ __forceinline__ u32x4 pack8(const float (&v)[8], float scale) {
-  u32x4 w;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) w[p] = pack_bf16(v[2 * p] * scale, v[2 * p + 1] * scale);
-  return w;
-}
 
 struct TileWalk {
   int tiles_per_row, total, H;
@@ -455,14 +449,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_vmod_fwd_mfma(Geom g, const unsi
 // u-hat (1) and of the other map's (2, both packed fp16).  Only the result stays in registers; the
 // second pass must really load again (its loader is handed pass = 1 so that it can use an address
 // the compiler cannot match with the first pass's).
-// fDU: this lane's token row of that factor array (see VmodFactors; + 8 gl already applied), or
+// fT: this lane's token row of that factor array (see VmodFactors; + 8 gl already applied), or
 // nullptr.  ag / ab (D / 2 entries; 1 entry: no sums wanted): the lane's running sums of dm * u-hat and of dm over its
 // tokens, entry 8 ks + j for channel 16 ks + 8 gl + j; `live` is 1 for a token of the sequence
 // and 0 for the padding of a ragged tile, whose rows must not be counted.
 template <int D, int NA, class Load>
 __device__ __forceinline__ float norm_backward(const unsigned char* wm_self, const unsigned char* wm_other,
                                                int gl, Load&& load, float rstd, u32x4 (&dub)[D / 16],
-                                               bf16_t* fDU, float (&ag)[NA], float (&ab)[NA], float live) {
+                                               uint16_t* fT, float (&ag)[NA], float (&ab)[NA], float live) {
   static_assert(NA == D / 2 || NA == 1, "the lane's 64 channels, or no sums wanted");
   using SM = VSmem<D>;
   constexpr int NKS = D / 16;
@@ -531,7 +525,7 @@ __device__ __forceinline__ float norm_backward(const unsigned char* wm_self, con
     for (int j = 0; j < 8; ++j) tv[j] = __builtin_fmaf(gg[j], inv, -a) - uh[j] * bq;
 #pragma unroll
     for (int p = 0; p < 4; ++p) dub[ks][p] = __builtin_bit_cast(uint32_t, to_f16x2(tv[2 * p], tv[2 * p + 1]));
-    if (fDU != nullptr) *reinterpret_cast<u32x4*>(fDU + 16 * ks) = pack8(tv, rstd * nrm);
+    if (fT != nullptr) *reinterpret_cast<u32x4*>(fT + 16 * ks) = dub[ks];
     if constexpr (NA == D / 2) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -553,10 +547,7 @@ template <int D>
 __device__ __forceinline__ void map_backward(const unsigned char* wm, const int (&a_off)[D / 16],
                                              const int (&t_off)[2][D / 32], int gl,
                                              const u32x4 (&x)[D / 16], const u32x4 (&dub)[D / 16],
-                                             f32x16 (&dx)[D / 32], bf16_t* fG = nullptr,
-                                             bf16_t* fDH = nullptr, float scale = 1.0f) {
-  // fG / fDH: this lane's token rows of the factor arrays (+ 8 gl applied) or nullptr; `scale` is
-  // the factor the normalised du (and with it dh) is short of
+                                             f32x16 (&dx)[D / 32]) {
   using SM = VSmem<D>;
   constexpr int NRB = D / 32, NKS = D / 16;
   auto tr_operand = [&](const unsigned char* mat, int blk, int ks) {
@@ -609,25 +600,6 @@ __device__ __forceinline__ void map_backward(const unsigned char* wm, const int 
 #pragma unroll
     for (int p = 0; p < 8; ++p)
       dhb[p / 4][p % 4] = pack_bf16(static_cast<float>(gp[p][0]) * dg[2 * p], static_cast<float>(gp[p][1]) * dg[2 * p + 1]);
-    if (fG != nullptr) {  // registers 8 hf .. 8 hf + 7 of the block are channels 32 hb + 16 hf + 8 gl ..
-      uint32_t gq[8];
-      gelu_y16<4>(reinterpret_cast<const f16x2(&)[4]>(y[0]), reinterpret_cast<uint32_t(&)[4]>(gq[0]));
-      gelu_y16<4>(reinterpret_cast<const f16x2(&)[4]>(y[4]), reinterpret_cast<uint32_t(&)[4]>(gq[4]));
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        float gv[8], hv[8];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const f16x2 g2 = __builtin_bit_cast(f16x2, gq[4 * hf + p]);
-          gv[2 * p] = static_cast<float>(g2[0]);
-          gv[2 * p + 1] = static_cast<float>(g2[1]);
-          hv[2 * p] = static_cast<float>(gp[4 * hf + p][0]) * dg[8 * hf + 2 * p];
-          hv[2 * p + 1] = static_cast<float>(gp[4 * hf + p][1]) * dg[8 * hf + 2 * p + 1];
-        }
-        *reinterpret_cast<u32x4*>(fG + 32 * hb + 16 * hf) = pack8(gv, 1.0f / kHiddenScale);
-        *reinterpret_cast<u32x4*>(fDH + 32 * hb + 16 * hf) = pack8(hv, scale * kHiddenScale);  // dg carries the packed W2's factor 4
-      }
-    }
     if (hb + 1 < NRB) {
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) ag[ks] = tr_operand(wm + SM::kW2, hb + 1, ks);
@@ -721,16 +693,17 @@ __global__ __launch_bounds__(WAVES * 64, FACTORS ? 1 : 2) void k_vmod_bwd_map(Ge
       const int m = which == 1 ? MAP : 1 - MAP;
       return load_global16(slot_rd[pass] + (m * NKS + ks) * 1024 + lane16);
     };
-    const int64_t frow = FACTORS && n0 + r < g.N ? g.th(b, h, n0 + r) * D + 8 * gl : -1;
-    auto frow_of = [&](bf16_t* base) -> bf16_t* { return FACTORS && frow >= 0 ? base + frow : nullptr; };
+    const int64_t frow = FACTORS && n0 + r < g.N ? g.th(b, h, n0 + r) : -1;
     u32x4 x[NKS];  // the map's input rows, for the first layer's recomputation
     load_row<D>(X, b, h, n0 + r, g.N, gl, x);
     u32x4 du[NKS];
-    const float sc = norm_backward<D>(smem, wm_other, gl, loader, rstd, du, frow_of(fac.dU[MAP]), ag, ab,
+    const float sc = norm_backward<D>(smem, wm_other, gl, loader, rstd, du,
+                                      FACTORS && frow >= 0 ? fac.t[MAP] + frow * D + 8 * gl : nullptr, ag, ab,
                                       frow >= 0 ? 1.0f : 0.0f);
+    if (FACTORS && frow >= 0 && gl == 0) fac.scale[MAP][frow] = sc;
     __builtin_amdgcn_sched_barrier(0);
     f32x16 dx[NRB];
-    map_backward<D>(smem, a_off, t_off, gl, x, du, dx, frow_of(fac.G[MAP]), frow_of(fac.dH[MAP]), sc);
+    map_backward<D>(smem, a_off, t_off, gl, x, du, dx);
     __builtin_amdgcn_sched_barrier(0);
     // what the result is added to: dO (MAP 0) or the operator's own dV (MAP 1), this lane's row
     load_row<D>(MAP == 0 ? dO : out, b, h, n0 + r, g.N, gl, x);
@@ -810,148 +783,271 @@ __global__ __launch_bounds__(256) void k_vmod_gb_reduce(const float* __restrict_
   }
 }
 
-// C[i][j] = sum over tokens of A[t][i] B[t][j] and z[i] = sum over tokens of A[t][i] for two bf16
-// [B, H, N, D] views, on the matrix cores.  grid (parts, D / 64, jobs), block 256: workgroup half
-// blockIdx.y owns rows 64 y .. 64 y + 63 of C; each wave streams 64-token sub-tiles (both row tiles
-// through its private LDS, both operands by transpose reads, k = token) of the flat list over all
-// (batch row, head) pairs; the workgroup writes one partial:
-//   part[(job * parts + blockIdx.x) * (D / 64) + y] = [C rows 64 x D | z 64] floats (the four waves
-//   summed in order).  grid.z = jobs: the (A, B) pairs of the list.
+// ---- weight gradients of the two layers ---------------------------------------------------------------
+// With y the first layer's output / 4, t and s what the backward kernel left of a token (see VmodFactors):
+//   dU = s t,  dH = GELU'(4y) * s (t W2^T),  G = GELU(4y):
+//   dW1 = X^T dH, db1 = sum dH, dW2 = G^T dU, db2 = sum dU          (sums over all tokens)
+// for map blockIdx.y.  A token is an MFMA row here (as in the feature maps' weight gradients): the
+// hidden layer leaves its unit in a lane and its tokens in the accumulator registers, which is the
+// operand the contractions over tokens want, so dH and G never leave the registers.
+// Waves w and w + 4 share a SIMD and a block of 32 hidden units whose weights they keep in registers;
+// the first forms dH and dW1, the second G and dW2 (both compute the block's first layer).  The 64-token
+// tiles of X, t and bf16 dU are shared by the waves of a group in LDS, two buffers, loaded through
+// registers a tile ahead; one barrier per tile.  A group (512 threads at D = 128, 256 at D = 64) ends
+// with one partial: [dW1 (in, hidden) | dW2 transposed (out, hidden) | db1 | db2] floats.
+// With the backward writing dU, dH and G and a kernel that contracted them from memory (each array read
+// twice), a map cost 242 us in the backward, and the contractions and their sums 214 + 22 us, at 12 heads
+// x 32760 tokens x 128 channels; now 203 a map, 188 + 7.  No unit is busy more than half of the time: a
+// wave's LDS reads, matrix chain, GELU and second chain follow each other, and two waves share a SIMD.
 template <int D>
-struct TnSmem {
-  static constexpr int kStride = D * 2 + 32;
-  static constexpr int kTile = 64 * kStride;
-  static constexpr int kTotal = 4 * 2 * kTile;
+struct VWgSmem {
+  static constexpr int kTok = 64;
+  static constexpr int kRows = kTok * D * 2;                   // one tile of one array
+  static constexpr int kScale = 3 * kRows;                     // X, t, dU, then the tokens' scales
+  static constexpr int kBuf = kScale + kTok * 4;
+  static constexpr int kGroups = 128 / D;
+  static constexpr int kTotal = kGroups * 2 * kBuf;
+  static constexpr int kPart = 2 * D * D + 2 * D;              // floats of a partial
 };
-// The token contractions of one backward as a list: one launch forms them all (blockIdx.z picks
-// the job), a second one adds up the partials of each.
-constexpr int kTnJobs = 4;
-struct TnJob {
-  View A, Bv;
-  float* M;
-  float* v;
-};
-struct TnJobs {
-  TnJob j[kTnJobs];
-};
+constexpr int kWgBlocks = 128;  // workgroups per map: one per compute unit
+
 template <int D>
-__global__ __launch_bounds__(256) void k_tn_mfma(Geom g, TnJobs jobs, float* __restrict__ part) {
-  using SM = TnSmem<D>;
-  const View A = jobs.j[blockIdx.z].A, Bv = jobs.j[blockIdx.z].Bv;
-  constexpr int NCB = D / 32;
-  extern __shared__ __align__(16) unsigned char smem[];
+__global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned char* __restrict__ wpk, View Tin, View V,
+                                                       VmodFactors fac, float* __restrict__ part) {
+  using SM = VWgSmem<D>;
+  using PK = VPacked<D>;
+  constexpr int NRB = D / 32, NKS = D / 16, kPieces = D / 8, kThreads = 2 * NRB * 64;  // of a group
+  static_assert(SM::kTok * kPieces == 2 * kThreads, "two 16-byte pieces of a tile per thread");
+  extern __shared__ __align__(256) unsigned char smem[];
   const int lane = threadIdx.x % kWave, wave = wave_index();
-  unsigned char* as = smem + wave * 2 * SM::kTile;
-  unsigned char* bs = as + SM::kTile;
-  const int r = lane % 32, gq = lane / 32, L = lane % 16, q = lane / 16;
-  const int half = blockIdx.y;
-  f32x16 acc[2][NCB], zacc[2];
+  const int r = lane % 32, gl = lane / 32;
+  const int L = lane % 16, q = lane / 16;
+  const int role = wave / 4, grp = wave % 4 / NRB, hb = wave % NRB;
+  const int m = blockIdx.y;
+  unsigned char* bufs = smem + grp * 2 * SM::kBuf;
+  const unsigned char* wm = wpk + m * PK::kBytes;
+  const View& X = m == 0 ? Tin : V;
+  const uint16_t* __restrict__ tarr = fac.t[m];
+  const float* __restrict__ sarr = fac.scale[m];
+  // rows 32 hb + r of W1^T or W2, k-slot (ks, gl, j) = column 16 ks + 8 gl + j
+  auto weight_rows = [&](int mat, u32x4 (&w)[NKS]) {
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) zacc[rb][i] = 0.0f;
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[rb][cb][i] = 0.0f;
-  }
-  u32x4 ones;
-  ones[0] = ones[1] = ones[2] = ones[3] = 0x3f803f80u;  // bf16 1.0 pairs
-  const int per_row = (g.N + 63) / 64;
-  const int total = per_row * g.B * g.H;
-  const int stride = gridDim.x * 4;
-  TileRegs<D, 64> ta, tb;
-  auto fetch = [&](int st) {
-    const int row = st / per_row, n0 = (st % per_row) * 64;
-    fetch_tile<D, 64>(A, row / g.H, row % g.H, n0, g.N, lane, ta);
-    fetch_tile<D, 64>(Bv, row / g.H, row % g.H, n0, g.N, lane, tb);
+    for (int ks = 0; ks < NKS; ++ks)
+      w[ks] = *reinterpret_cast<const u32x4*>(wm + mat + ((32 * hb + r) * D + 16 * ks + 8 * gl) * 2);
   };
-  int st = blockIdx.x * 4 + wave;
-  if (st < total) fetch(st);
-  for (; st < total; st += stride) {
-    put_tile<D, 64>(ta, lane, as, SM::kStride);
-    put_tile<D, 64>(tb, lane, bs, SM::kStride);
-    if (st + stride < total) fetch(st + stride);
-    wave_lds_sync();
+  u32x4 w1b[NKS];
+  weight_rows(PK::kW1T, w1b);
+  const float bias = *reinterpret_cast<const float*>(wm + PK::kB1 + (32 * hb + r) * 4);
+  // this thread's share of a tile: 16-byte piece `piece` of tokens tok and tok + 32
+  const int tid = (role * NRB + hb) * 64 + lane, piece = tid % kPieces, tok = tid / kPieces;
+  const int tpr = (g.N + SM::kTok - 1) / SM::kTok;
+  const int total = tpr * g.B * g.H;
+  u32x4 xr[2], tr[2];
+  float sr[2];
+  float db2[8];  // of channels 8 piece .. + 7, over this thread's tokens
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int krow = 16 * ks + 8 * gq + L / 4;  // token row this lane addresses for the transpose reads
-      u32x4 a[2];
+  for (int e = 0; e < 8; ++e) db2[e] = 0.0f;
+  auto fetch = [&](int tile) {  // every address is valid; what must not count has scale and t zero
+    const int tc = tile < total ? tile : total - 1;
+    const int row = tc / tpr, n0 = (tc % tpr) * SM::kTok, b = row / g.H, h = row % g.H;
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        const unsigned char* p = as + krow * SM::kStride + (64 * half + 32 * rb + 16 * (q % 2) + 4 * (L % 4)) * 2;
-        const u32x2 lo = lds_read_tr16(p);
-        const u32x2 hi = lds_read_tr16(p + 4 * SM::kStride);
-        a[rb][0] = lo[0];
-        a[rb][1] = lo[1];
-        a[rb][2] = hi[0];
-        a[rb][3] = hi[1];
-      }
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const unsigned char* p = bs + krow * SM::kStride + (32 * cb + 16 * (q % 2) + 4 * (L % 4)) * 2;
-        const u32x2 lo = lds_read_tr16(p);
-        const u32x2 hi = lds_read_tr16(p + 4 * SM::kStride);
-        u32x4 b;
-        b[0] = lo[0];
-        b[1] = lo[1];
-        b[2] = hi[0];
-        b[3] = hi[1];
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) acc[rb][cb] = mfma32(a[rb], b, acc[rb][cb]);
-      }
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) zacc[rb] = mfma32(a[rb], ones, zacc[rb]);
+    for (int k = 0; k < 2; ++k) {
+      const int n = n0 + tok + 32 * k, nc = n < g.N ? n : g.N - 1;
+      const int64_t th = g.th(b, h, nc);
+      xr[k] = *reinterpret_cast<const u32x4*>(X.row<const bf16_t>(b, h, nc) + 8 * piece);
+      tr[k] = *reinterpret_cast<const u32x4*>(tarr + th * D + 8 * piece);
+      sr[k] = sarr[th];
     }
-    wave_lds_sync();
+  };
+  auto put = [&](int tile, unsigned char* buf) {
+    const int n0 = (tile % tpr) * SM::kTok;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int t = tok + 32 * k, at = tile_off<D * 2>(t, piece);
+      const bool live = tile < total && n0 + t < g.N;
+      u32x4 tv = tr[k], u;
+      const float sv = live ? sr[k] : 0.0f;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        if (!live) tv[p] = 0u;
+        const uint32_t w = tv[p];
+        const f16x2 t2 = __builtin_bit_cast(f16x2, w);
+        const float u0 = static_cast<float>(t2[0]) * sv, u1 = static_cast<float>(t2[1]) * sv;
+        db2[2 * p] += u0;
+        db2[2 * p + 1] += u1;
+        u[p] = pack_bf16(u0, u1);
+      }
+      *reinterpret_cast<u32x4*>(buf + at) = xr[k];
+      *reinterpret_cast<u32x4*>(buf + SM::kRows + at) = tv;
+      *reinterpret_cast<u32x4*>(buf + 2 * SM::kRows + at) = u;
+      if (piece == 0) *reinterpret_cast<float*>(buf + SM::kScale + t * 4) = sv;
+    }
+  };
+  // LDS addresses: row r, chunk 2 ks + gl of the layers' operands; transpose reads whose k-slot (gl, j) of
+  // step ks is token 16 ks + 8 (j / 4) + 4 gl + j % 4, the order the accumulators hold
+  int a_off[NKS], t_off[2][NRB];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) a_off[ks] = tile_off<D * 2>(r, 2 * ks + gl);
+#pragma unroll
+  for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) {
+      const int row = 4 * gl + 8 * hi + L / 4, col = 32 * ib + 16 * (q % 2) + 4 * (L % 4);
+      t_off[hi][ib] = tile_off<D * 2>(row, col >> 3) + ((col & 7) << 1);
+    }
+  f32x16 acc[NRB];  // role 0: dW1 rows 32 ib + d_row(i, gl), role 1: dW2^T rows, column 32 hb + r
+  float db1 = 0.0f;
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[ib][i] = 0.0f;
+  // acc += (rows of `tile` transposed) * v over the 32 tokens of a sub-tile
+  auto contract = [&](const unsigned char* tile, const u32x4 (&v)[2]) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      u32x4 a[NRB];
+      __builtin_amdgcn_sched_barrier(0);  // no operand read early: registers are short
+#pragma unroll
+      for (int ib = 0; ib < NRB; ++ib) {
+        const u32x2 lo = lds_read_tr16(tile + 16 * ks * D * 2 + t_off[0][ib]), hi = lds_read_tr16(tile + 16 * ks * D * 2 + t_off[1][ib]);
+        a[ib][0] = lo[0];
+        a[ib][1] = lo[1];
+        a[ib][2] = hi[0];
+        a[ib][3] = hi[1];
+      }
+#pragma unroll
+      for (int ib = 0; ib < NRB; ++ib) acc[ib] = mfma32(a[ib], v[ks], acc[ib]);
+    }
+  };
+  auto first_layer = [&](const unsigned char* xs) {
+    f32x16 y;
+    float bv = bias;
+    asm volatile("" : "+v"(bv));  // else the sixteen copies are kept in registers across the loop
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i] = bv;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) y = mfma32(*reinterpret_cast<const u32x4*>(xs + a_off[ks]), w1b[ks], y);
+    return y;
+  };
+  const int step = gridDim.x * SM::kGroups, first = blockIdx.x * SM::kGroups;
+  const int iters = (total - first + step - 1) / step;  // of group 0, which has the most
+  // the loop over tiles of one role: code of its own for each, so that a role pays for its own registers only
+  auto run = [&](auto DH) {
+    int tile = first + grp;
+    u32x4 w2b[NKS];
+    if constexpr (DH.value) weight_rows(PK::kW2, w2b);
+    fetch(tile);
+    put(tile, bufs);
+    fetch(tile + step);
+    __syncthreads();
+    for (int it = 0; it < iters; ++it, tile += step) {
+      const unsigned char* buf = bufs + (it % 2) * SM::kBuf;
+#pragma unroll 1
+      for (int sub = 0; sub < 2; ++sub) {
+        const unsigned char* xs = buf + sub * 32 * D * 2;
+        const unsigned char* ts = xs + SM::kRows;
+        const unsigned char* us = xs + 2 * SM::kRows;
+        u32x4 v[2];
+        if constexpr (DH.value) {
+          f32x16 dg;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) dg[i] = 0.0f;
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks) dg = mfma32_f16(*reinterpret_cast<const u32x4*>(ts + a_off[ks]), w2b[ks], dg);
+          asm volatile("" : "+v"(dg) : : "memory");  // the first layer's operands are read after this: registers are short
+          const f32x16 y = first_layer(xs);
+          __builtin_amdgcn_sched_barrier(0);
+          f32x4 sc[4];  // of tokens 8 i + 4 gl + 0 .. 3
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[i] = *reinterpret_cast<const f32x4*>(buf + SM::kScale + (32 * sub + 8 * i + 4 * gl) * 4);
+          f16x2 yh[8], gp[8];
+#pragma unroll
+          for (int p = 0; p < 8; ++p) yh[p] = to_f16x2(y[2 * p], y[2 * p + 1]);
+          gelu_grad_y16<8>(yh, gp);
+#pragma unroll
+          for (int p = 0; p < 8; ++p) {
+            const float d0 = static_cast<float>(gp[p][0]) * (dg[2 * p] * sc[p / 2][2 * (p % 2)]);
+            const float d1 = static_cast<float>(gp[p][1]) * (dg[2 * p + 1] * sc[p / 2][2 * (p % 2) + 1]);
+            db1 += d0 + d1;
+            v[p / 4][p % 4] = pack_bf16(d0, d1);
+          }
+          contract(xs, v);
+        } else {
+          const f32x16 y = first_layer(xs);
+          f16x2 yh[8];
+          uint32_t gq[8];
+#pragma unroll
+          for (int p = 0; p < 8; ++p) yh[p] = to_f16x2(y[2 * p], y[2 * p + 1]);
+          gelu_y16<8>(yh, gq);
+#pragma unroll
+          for (int p = 0; p < 8; ++p) {
+            const f16x2 g2 = __builtin_bit_cast(f16x2, gq[p]);
+            v[p / 4][p % 4] = pack_bf16(static_cast<float>(g2[0]), static_cast<float>(g2[1]));
+          }
+          contract(us, v);
+        }
+      }
+      // the buffer of the tile before this one, which every wave left before the last barrier
+      put(tile + step, bufs + ((it + 1) % 2) * SM::kBuf);
+      fetch(tile + 2 * step);
+      __syncthreads();
+    }
+  };
+  if (role == 0)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+  float* out = part + (static_cast<int64_t>(m) * gridDim.x * SM::kGroups + blockIdx.x * SM::kGroups + grp) * SM::kPart;
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) out[role * D * D + (32 * ib + d_row(i, gl)) * D + 32 * hb + r] = acc[ib][i];
+  db1 += partner32(db1);
+  if (role == 0 && gl == 0) out[2 * D * D + 32 * hb + r] = db1;
+  // db2 over the 32 threads of a piece (the tiles are done with)
+  float* red = reinterpret_cast<float*>(bufs);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[tok * (D + 1) + 8 * piece + e] = db2[e];
+  __syncthreads();
+  if (tid < D) {
+    float sum = 0.0f;
+    for (int k = 0; k < 32; ++k) sum += red[k * (D + 1) + tid];
+    out[2 * D * D + D + tid] = sum;
   }
-  // the four waves' sums through LDS (the row tiles are done with), added in wave order, one
-  // partial per workgroup
-  constexpr int PW = 64 * D + 64;
-  static_assert(4 * PW * 4 <= SM::kTotal, "the waves' tiles fit the LDS the row tiles used");
-  __syncthreads();
-  float* mine = reinterpret_cast<float*>(smem) + wave * PW;
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = 32 * rb + d_row(i, gq);
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) mine[row * D + 32 * cb + r] = acc[rb][cb][i];
-      if (r == 0) mine[64 * D + row] = zacc[rb][i];
-    }
-  __syncthreads();
-  const float* all = reinterpret_cast<const float*>(smem);
-  float* out = part + ((static_cast<int64_t>(blockIdx.z) * gridDim.x + blockIdx.x) * gridDim.y + half) * PW;
-  for (int k = threadIdx.x; k < PW; k += 256) out[k] = ((all[k] + all[PW + k]) + all[2 * PW + k]) + all[3 * PW + k];
 }
 
-// Adds the `nparts` partials of k_tn_mfma in order: M[j * D + i] = C[i][j] (the transpose: the
-// products are formed with the gradient as the A operand) and v[i] = z[i].
-// grid (D * D / 256, jobs), block 256.
+// Adds the `nparts` partials of k_vmod_wgrad in a fixed order, undoes the packing factors (the first layer
+// and with it GELU are a quarter of their scale, t W2^T four times it) and puts dW2 the right way round.
+// Four slices of the partials per output, sixteen loads in flight each.  grid (kPart / 64, 2 maps), block 256.
 template <int D>
-__global__ void k_tn_reduce(const float* __restrict__ part, int nparts, TnJobs jobs) {
-  constexpr int HALVES = D / 64;
-  constexpr int64_t PW = 64 * D + 64;
-  float* __restrict__ M = jobs.j[blockIdx.y].M;
-  float* __restrict__ v = jobs.j[blockIdx.y].v;
-  const int idx = blockIdx.x * 256 + threadIdx.x;  // i * D + j
-  const int i = idx / D, j = idx % D;
-  const float* base = part + (static_cast<int64_t>(blockIdx.y) * nparts * HALVES + i / 64) * PW;
-  // eight partials' loads in flight at a time, added in order
-  auto sum = [&](int64_t off) {
-    float s = 0.0f;
-    for (int p = 0; p < nparts; p += 8) {
-      float ld[8];
+__global__ __launch_bounds__(256) void k_vmod_wgrad_reduce(const float* __restrict__ part, int nparts,
+                                                           hla_vmod_weight_grads o0, hla_vmod_weight_grads o1) {
+  constexpr int64_t PW = VWgSmem<D>::kPart;
+  __shared__ float sh[4][64];
+  const int c = threadIdx.x % 64, slice = threadIdx.x / 64, idx = blockIdx.x * 64 + c;
+  const hla_vmod_weight_grads& o = blockIdx.y == 0 ? o0 : o1;
+  const float* base = part + static_cast<int64_t>(blockIdx.y) * nparts * PW + idx;
+  const int per = (nparts + 3) / 4, p0 = slice * per, p1 = p0 + per < nparts ? p0 + per : nparts;
+  float sum = 0.0f;
+  for (int p = p0; p < p1; p += 16) {
+    float ld[16];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) ld[k] = p + k < nparts ? base[static_cast<int64_t>(p + k) * HALVES * PW + off] : 0.0f;
+    for (int k = 0; k < 16; ++k) ld[k] = p + k < p1 ? base[(p + k) * PW] : 0.0f;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) s += ld[k];
-    }
-    return s;
-  };
-  M[j * D + i] = sum((i % 64) * D + j);
-  if (j == 0) v[i] = sum(64 * D + i % 64);
+    for (int k = 0; k < 16; ++k) sum += ld[k];
+  }
+  sh[slice][c] = sum;
+  __syncthreads();
+  if (slice != 0) return;
+  sum = ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
+  if (idx < D * D)
+    o.dW1[idx] = sum * kHiddenScale;
+  else if (idx < 2 * D * D)
+    o.dW2[(idx % D) * D + (idx - D * D) / D] = sum * (1.0f / kHiddenScale);
+  else if (idx < 2 * D * D + D)
+    o.db1[idx - 2 * D * D] = sum * kHiddenScale;
+  else
+    o.db2[idx - 2 * D * D - D] = sum;
 }
 
 template <int D>
@@ -966,8 +1062,8 @@ hla_status prepare_t() {
                                   hipFuncAttributeMaxDynamicSharedMemorySize, VSmemB<D>::total_factors(kWavesV)));
   HLA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_vmod_bwd_map<D, kWavesV, true, 1>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, VSmemB<D>::total_factors(kWavesV)));
-  HLA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tn_mfma<D>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, TnSmem<D>::kTotal));
+  HLA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_vmod_wgrad<D>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, VWgSmem<D>::kTotal));
   return HLA_OK;
 }
 
@@ -988,17 +1084,14 @@ hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
                 hd->vmod_ln_eps, vmod_view(hd->vmod_T, g), a.V, a.O, hd->vmod_wpk + vmod_mfma_packed_bytes(hd));
 }
 
-// the six factor arrays inside hd->vmod_wg_rows (bf16 [max_th][d] each); the workgroups' partial
-// sums of dgamma and dbeta go to the head of the contractions' partial buffer, which is free while
-// the backward kernels run
+// the factor arrays inside hd->vmod_wg_rows; the workgroups' partial sums of dgamma and dbeta go to the
+// head of the contractions' partial buffer, which is free while the backward kernels run
 VmodFactors factor_arrays(const hla_handle* hd) {
   VmodFactors f;
-  bf16_t* base = reinterpret_cast<bf16_t*>(hd->vmod_wg_rows);
   const int64_t per = hd->max_th * hd->g.d;
   for (int m = 0; m < 2; ++m) {
-    f.dU[m] = base + (3 * m + 0) * per;
-    f.dH[m] = base + (3 * m + 1) * per;
-    f.G[m] = base + (3 * m + 2) * per;
+    f.t[m] = reinterpret_cast<uint16_t*>(hd->vmod_wg_rows) + m * per;
+    f.scale[m] = hd->vmod_wg_rows + per + m * hd->max_th;  // behind two 16-bit arrays
   }
   f.gb_part = hd->vmod_wg_partial;
   return f;
@@ -1030,24 +1123,17 @@ hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
   return backward_map_t<D, 0>(hd, a, vmod_view(hd->vmod_dT, hd->g));
 }
 
-constexpr int kTnBlocks = 128;  // workgroups (and partials) per row half of a token contraction
-
 template <int D>
 hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
+  using SM = VWgSmem<D>;
   const Geom& g = hd->g;
-  const VmodFactors f = factor_arrays(hd);
-  TnJobs jobs;
-  for (int m = 0; m < 2; ++m) {
-    const hla_vmod_weight_grads& o = hd->vmod_wg_out[m];
-    jobs.j[2 * m + 0] = TnJob{vmod_view(f.dU[m], g), vmod_view(f.G[m], g), o.dW2, o.db2};
-    jobs.j[2 * m + 1] = TnJob{vmod_view(f.dH[m], g), m == 0 ? vmod_view(hd->vmod_T, g) : a.V, o.dW1, o.db1};
-  }
-  const int64_t subtiles = static_cast<int64_t>((g.N + 63) / 64) * g.B * g.H;
-  const int blocks = static_cast<int>(std::min<int64_t>(kTnBlocks, (subtiles + 3) / 4));
-  HLA_TRY(launch(hd, "vmod_weight_grads_gemm", k_tn_mfma<D>, dim3(blocks, D / 64, kTnJobs), dim3(256),
-                 TnSmem<D>::kTotal, a.stream, g, jobs, hd->vmod_wg_partial));
-  return launch(hd, "vmod_weight_grads_reduce", k_tn_reduce<D>, dim3(D * D / 256, kTnJobs), dim3(256), 0, a.stream,
-                static_cast<const float*>(hd->vmod_wg_partial), blocks, jobs);
+  const int64_t tiles = static_cast<int64_t>((g.N + SM::kTok - 1) / SM::kTok) * g.B * g.H;
+  const int blocks = static_cast<int>(std::min<int64_t>(kWgBlocks, (tiles + SM::kGroups - 1) / SM::kGroups));
+  HLA_TRY(launch(hd, "vmod_weight_grads_gemm", k_vmod_wgrad<D>, dim3(blocks, 2), dim3(512), SM::kTotal, a.stream, g,
+                 static_cast<const unsigned char*>(hd->vmod_wpk), vmod_view(hd->vmod_T, g), a.V, factor_arrays(hd),
+                 hd->vmod_wg_partial));
+  return launch(hd, "vmod_weight_grads_reduce", k_vmod_wgrad_reduce<D>, dim3((2 * D * D + 2 * D) / 64, 2), dim3(256), 0, a.stream,
+                static_cast<const float*>(hd->vmod_wg_partial), blocks * SM::kGroups, hd->vmod_wg_out[0], hd->vmod_wg_out[1]);
 }
 
 template <int D>
@@ -1095,9 +1181,10 @@ hla_status vmod_mfma_weight_grads(hla_handle* hd, const hla_call_args& a) {
   return hd->g.d == 64 ? weight_grads_t<64>(hd, a) : weight_grads_t<128>(hd, a);
 }
 // floats the factor arrays and the partials of the contractions need
-int64_t vmod_mfma_factor_floats(const hla_handle* hd) { return 3 * hd->max_th * hd->g.d; }  // six bf16 arrays
+int64_t vmod_mfma_factor_floats(const hla_handle* hd) { return hd->max_th * (hd->g.d + 2); }
 int64_t vmod_mfma_partial_floats(const hla_handle* hd) {
-  return static_cast<int64_t>(kTnJobs) * kTnBlocks * (hd->g.d / 64) * (64 * hd->g.d + 64);
+  const int64_t groups = hd->g.d == 64 ? VWgSmem<64>::kGroups : VWgSmem<128>::kGroups;
+  return 2 * kWgBlocks * groups * (2 * hd->g.d * hd->g.d + 2 * hd->g.d);
 }
 hla_status vmod_mfma_add_value_grads(hla_handle* hd, const hla_call_args& a) {
   return hd->g.d == 64 ? add_t<64>(hd, a) : add_t<128>(hd, a);

@@ -97,6 +97,17 @@ def test_modulation_weight_gradients(dtype, path, F, dphi, d, B, H, N, tol):
         assert torch.equal(gpu[k], plain[k]), k
 
 
+@pytest.mark.parametrize("d,H,N", [(128, 1, 64), (128, 1, 65), (128, 3, 191), (64, 1, 64), (64, 1, 63), (64, 3, 129)])
+def test_modulation_weight_gradients_at_tile_edges(d, H, N):
+    """Around the 64-token tiles of the matrix-core contraction: a full and a nearly full tile, one token
+    more, an odd number of tiles for two groups of waves (one tile leaves the second without any)."""
+    t, phi = wl.make_raw_inputs(1190 + N + d, 1, H, N, d, 3, 6, torch.bfloat16)
+    vm = _vmod(1191 + N, d, torch.bfloat16)
+    gpu = pu.run_gpu(t, 3, 6, 1e-6, phi=phi, vmod=vm, vmod_weight_grads=True)
+    ref = pu.run_oracle(t, 3, 6, 1e-6, phi=phi, vmod=vm, vmod_weight_grads=True)
+    pu.assert_vmod_weight_grad_parity(gpu["vwg"], ref["vwg"], 2e-2, f"modulation weight grads d={d} H={H} N={N}")
+
+
 def test_modulation_weight_gradients_registration_rules():
     dev = torch.device("cuda:0")
     t = wl.make_feature_inputs(1170, 1, 2, 100, 64, 3, 6, torch.bfloat16)
