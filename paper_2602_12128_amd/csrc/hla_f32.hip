@@ -415,9 +415,9 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_state(Geom g, F32
                        partial + (static_cast<int64_t>(blockIdx.x) * g.H + h) * x.stride);
 }
 
-// ---- sum of the partial states of each (sequence, head), in run order ------------------------------
-// grid (num_seqs, H, slices), block 256; sixteen loads in flight (a run's load next to its addition
-// would cost a memory round trip per run).
+// ---- sum of the partial states of each (sequence, head), in a fixed order ------------------------------
+// grid (num_seqs, H, ceil(stride / 64)), block 256: four slices of the runs per element, sixteen loads in
+// flight each (a run's load next to its addition would cost a memory round trip per run).
 __global__ __launch_bounds__(256) void k_f32_reduce(int H, const int32_t* __restrict__ seq_off,
                                                     const float* __restrict__ partial, float* __restrict__ state,
                                                     int64_t stride) {
@@ -426,18 +426,22 @@ __global__ __launch_bounds__(256) void k_f32_reduce(int H, const int32_t* __rest
   const int64_t step = H * stride;
   const float* src = partial + (static_cast<int64_t>(c0) * H + h) * stride;
   float* out = state + (static_cast<int64_t>(s) * H + h) * stride;
-  for (int64_t i = blockIdx.z * 256 + threadIdx.x; i < stride; i += gridDim.z * 256) {
-    float a = 0.0f;
-    for (int c = 0; c < c1 - c0; c += 16) {
-      float v[16];
+  __shared__ float slices[4][64];
+  const int slice = threadIdx.x / 64;
+  const int64_t i = static_cast<int64_t>(blockIdx.z) * 64 + threadIdx.x % 64, at = min(i, stride - 1);
+  const int per = (c1 - c0 + 3) / 4, r0 = slice * per, r1 = min(r0 + per, c1 - c0);
+  float a = 0.0f;
+  for (int c = r0; c < r1; c += 16) {
+    float v[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = src[min(c + u, c1 - c0 - 1) * step + i];
+    for (int u = 0; u < 16; ++u) v[u] = src[min(c + u, r1 - 1) * step + at];
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (c + u < c1 - c0) a += v[u];
-    }
-    out[i] = a;
+    for (int u = 0; u < 16; ++u)
+      if (c + u < r1) a += v[u];
   }
+  slices[slice][threadIdx.x % 64] = a;
+  __syncthreads();
+  if (slice == 0 && i < stride) out[i] = ((a + slices[1][threadIdx.x]) + slices[2][threadIdx.x]) + slices[3][threadIdx.x];
 }
 
 // ---- query side: O = Qm C / (Qm z + eps) ------------------------------------------------------------
@@ -768,7 +772,7 @@ hla_status runs_table(hla_handle* hd, const hla_call_args& a, hla_token_table** 
 
 hla_status reduce_partials(hla_handle* hd, const hla_call_args& a, const F32Geom& x, const hla_token_table* runs,
                            const char* name, float* out) {
-  const int slices = static_cast<int>(std::min<int64_t>((x.stride + 255) / 256, 16));
+  const unsigned slices = static_cast<unsigned>((x.stride + 63) / 64);
   return launch(hd, name, k_f32_reduce, dim3(a.num_seqs, a.H, slices), dim3(256), 0, a.stream, a.H,
                 runs->seq_off_dev, static_cast<const float*>(hd->partial), out, x.stride);
 }
