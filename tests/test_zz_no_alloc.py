@@ -41,6 +41,27 @@ def test_static_forward_matches_handle_forward_and_oracle():
         pu.assert_parity({"O": got}, ref, pu.TOL[dtype], f"static forward case {i}")
 
 
+@pytest.mark.parametrize("F,dphi,d", [(3, 6, 128), (2, 12, 64)])
+def test_static_forward_reads_features_in_place(F, dphi, d):
+    """Feature rows on 4-byte addresses are read where they are, others are copied first; neither shows."""
+    for N in (1, 63, 65, 700):
+        t = wl.make_feature_inputs(970 + N, 2, 3, N, d, F, dphi, torch.bfloat16)
+        want = pu.run_gpu(t, F, dphi, 1e-6, backward=False)["O"]
+        td = {k: v.cuda() for k, v in t.items()}
+
+        def padded(x, pad, off):
+            buf = torch.full(x.shape[:3] + (x.shape[3] + pad,), 5.0, dtype=x.dtype, device="cuda")
+            v = buf[..., off:off + x.shape[3]]
+            v.copy_(x)
+            return v
+
+        for pad, off in ((0, 0), (4, 2), (3, 0), (2, 1)):
+            O = torch.full_like(td["V"], float("nan"))
+            hla.hla_forward_static(padded(td["Q"], pad, off), padded(td["K"], pad, off), td["V"], O, feature_dim=dphi,
+                                   degree=F, eps=1e-6, io_dtype=hla.HLA_BF16)
+            assert torch.equal(O.cpu(), want), (N, pad, off)
+
+
 def test_static_forward_limits():
     dev = torch.device("cuda:0")
     # a layout that does not fit the static array is refused and leaves the output alone
