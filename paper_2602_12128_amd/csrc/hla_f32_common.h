@@ -30,18 +30,29 @@ __device__ __forceinline__ f32x16 zero16() {
 }
 
 // Rows [t0, t0 + nt) of a caller's tensor into LDS as fp32, row stride LD floats; rows from nt on are
-// zero.  16-byte loads where the view's pointer and strides allow it (and LD keeps rows aligned).
+// zero.  16-byte loads where the view's pointer and strides allow it (16-byte writes if LD keeps rows
+// aligned), all of a thread's in flight together.
 template <int D, int TOK, int THREADS, int LD>
 __device__ __forceinline__ void stage_rows(const View& X, int b, int h, int t0, int nt, bool bf16, bool vec,
                                            float* dst) {
-  if (LD % 4 == 0 && vec && !bf16) {
-    constexpr int P = D / 4;  // float4 pieces per row
+  if (vec && !bf16) {
+    constexpr int P = D / 4, IT = TOK * P / THREADS;  // float4 pieces per row, of a thread
+    f32x4 v[IT];
 #pragma unroll
-    for (int i = 0; i < TOK * P / THREADS; ++i) {
+    for (int i = 0; i < IT; ++i) {
       const int idx = threadIdx.x + i * THREADS, t = idx / P, p = idx % P;
-      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (t < nt) v = *reinterpret_cast<const f32x4*>(X.row<const float>(b, h, t0 + t) + 4 * p);
-      *reinterpret_cast<f32x4*>(dst + t * LD + 4 * p) = v;
+      v[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (t < nt) v[i] = *reinterpret_cast<const f32x4*>(X.row<const float>(b, h, t0 + t) + 4 * p);
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int idx = threadIdx.x + i * THREADS, t = idx / P, p = idx % P;
+      if constexpr (LD % 4 == 0) {
+        *reinterpret_cast<f32x4*>(dst + t * LD + 4 * p) = v[i];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[t * LD + 4 * p + e] = v[i][e];
+      }
     }
     return;
   }

@@ -6,9 +6,10 @@
 // B-operand order (32 consecutive floats per half wave) with the next steps' loads in flight.
 //
 // At 12 heads x 4095 tokens x 64 channels, three factors, fp32 (us; before: a thread per hidden unit on
-// the vector ALU, an LDS read per multiply-add): forward 45 (147), backward with the weight gradients
-// 102 (197 + 491 for a second pass that recomputed the hidden layer), of which 11 and 27 are
-// matrix-pipe time; the rest is GELU (erff, expf), the phases' barriers and the weights' way from L2.
+// the vector ALU, an LDS read per multiply-add): forward 35 (147), backward with the weight gradients
+// 86 (197 + 491 for a second pass that recomputed the hidden layer), of which 11 and 27 are
+// matrix-pipe time; the rest is the phases' barriers, GELU and the weights' way from L2.  With erff,
+// expf and the weights loaded where they are used, 43 and 100.
 #include <algorithm>
 #include <cmath>
 
@@ -21,8 +22,20 @@ using namespace f32;
 
 constexpr int kTok = 64;
 
-__device__ __forceinline__ float gelu_erf(float h) {
-  return h * 0.5f * (1.0f + erff(h * 0.70710678118654752440f));
+// Phi(h) of the exact GELU, h Phi(h): Phi(-t) = 2^-(1 + P(t)) for t >= 0 with a degree-8 minimax fit of
+// P(t) = -log2(erfc(t / sqrt 2)) on [0, 5.9], weighted by what an error of P does to the GELU; beyond,
+// P keeps growing and Phi(-t) runs to zero as it should.  Without branches: erff takes its
+// two ranges one after the other when the lanes of a wave need both.  In fp32, over [-9, 9]: GELU within
+// 3.9e-7 (rms 5.7e-8) of the exact one, h 0.5 (1 + erf) with a correctly rounded erf 4.5e-7 (6.4e-8).
+__device__ __forceinline__ float normal_cdf(float h) {
+  constexpr float c[9] = {1.0f,           1.1511064f,      0.45919567f,     0.052539267f, -0.0071317810f,
+                          0.00019325814f, 0.00016142147f, -3.3898614e-05f, 2.3575092e-06f};
+  const float t = fabsf(h);
+  float p = c[8];
+#pragma unroll
+  for (int k = 7; k >= 0; --k) p = __builtin_fmaf(p, t, c[k]);
+  const float e = __builtin_amdgcn_exp2f(-p);
+  return h > 0.0f ? 1.0f - e : e;
 }
 
 template <int D>
@@ -39,6 +52,25 @@ template <int D>
 __device__ __forceinline__ void tile_pos(int tile, int& rb, int& cb) {
   rb = tile / PhiCfg<D>::NCB;
   cb = tile % PhiCfg<D>::NCB;
+}
+
+// use(s, v) for the batches s = 0, NB, .. < STEPS of weight operands that load(s, v) fetches, each batch in
+// flight while the one before is used.  Two sets take turns (a copy from one to the other would wait for
+// the loads), and the compiler must not move the loads down to where they are used, which it otherwise
+// does: d = 128, 4 heads x 3000 tokens with weight gradients, 208 us a step that way, 155 like this.
+template <int NB, int STEPS, class Load, class Use>
+__device__ __forceinline__ void weight_steps(float (&first)[NB], Load&& load, Use&& use) {
+  static_assert(STEPS % (2 * NB) == 0, "pairs of batches");
+  float second[NB];
+#pragma unroll 1
+  for (int s = 0; s < STEPS; s += 2 * NB) {
+    load(s + NB, second);
+    asm volatile("" ::: "memory");
+    use(s, first);
+    load(s + 2 * NB < STEPS ? s + 2 * NB : s, first);
+    asm volatile("" ::: "memory");
+    use(s + NB, second);
+  }
 }
 
 struct PhiCall {
@@ -75,65 +107,75 @@ __global__ __launch_bounds__(256) void k_f32_phi_fwd(PhiCall c, View Q, View K, 
   const int64_t mh = static_cast<int64_t>(m) * c.w.heads_w + hw;
   const float* W1 = c.w.W1 + mh * D * D;
   const float* W2 = c.w.W2 + mh * D * g.dphi;
-  stage_rows<D, kTok, 256, LD>(m == 0 ? Q : K, b, h, t0, nt, c.bf16, false, sm);
-  f32x16 acc[TPW];
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) acc[i] = zero16();
-  __syncthreads();
   int rb0, cb;
   tile_pos<D>(wave, rb0, cb);  // W is a multiple of NCB: a wave's tiles share their column block
   static_assert(W % NCB == 0, "one column block per wave");
   const bool busy = wave < NT;
+  // the first weights and the second layer's, up to sixteen features, travel with the tile's rows: a
+  // workgroup is one chain of memory round trips, and this makes it one shorter per kind
+  const int l16 = lane % 16, q = lane / 16;
+  const float* bp = W1 + hf * D + 32 * cb + r;
+  float bv[NB], w2v[D / 4];
+#pragma unroll
+  for (int s = 0; s < NB; ++s) bv[s] = busy ? bp[2 * s * D] : 0.0f;
+#pragma unroll
+  for (int s = 0; s < D / 4; ++s) w2v[s] = W2[(4 * s + q) * g.dphi + (l16 < g.dphi ? l16 : 0)];
+  const float bias = busy ? c.w.b1[mh * D + 32 * cb + r] : 0.0f;
+  const float b2v = c.w.b2[mh * g.dphi + (l16 < g.dphi ? l16 : 0)];
+  stage_rows<D, kTok, 256, LD>(m == 0 ? Q : K, b, h, t0, nt, c.bf16, m == 0 ? c.vec_q : c.vec_k, sm);
+  f32x16 acc[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) acc[i] = zero16();
+  __syncthreads();
   if (busy) {
-    const float* bp = W1 + hf * D + 32 * cb + r;
-    float bv[NB], bn[NB];
+    weight_steps<NB, D / 2>(bv, [&](int s, float (&v)[NB]) {
 #pragma unroll
-    for (int s = 0; s < NB; ++s) bv[s] = bp[2 * s * D];
-#pragma unroll 1
-    for (int s0 = 0; s0 < D / 2; s0 += NB) {
-      const int sn = s0 + NB < D / 2 ? s0 + NB : s0;
+      for (int t = 0; t < NB; ++t) v[t] = bp[2 * (s + t) * D];
+    }, [&](int s, const float (&v)[NB]) {
 #pragma unroll
-      for (int s = 0; s < NB; ++s) bn[s] = bp[2 * (sn + s) * D];
-#pragma unroll
-      for (int s = 0; s < NB; ++s)
+      for (int t = 0; t < NB; ++t)
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
-          acc[i] = mfma32(sm[(32 * (rb0 + i * W / NCB) + r) * LD + 2 * (s0 + s) + hf], bv[s], acc[i]);
-#pragma unroll
-      for (int s = 0; s < NB; ++s) bv[s] = bn[s];
-    }
+          acc[i] = mfma32(sm[(32 * (rb0 + i * W / NCB) + r) * LD + 2 * (s + t) + hf], v[t], acc[i]);
+    });
   }
   __syncthreads();
   if (busy) {
-    const float bias = c.w.b1[mh * D + 32 * cb + r];
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        sm[(32 * (rb0 + i * W / NCB) + mf::d_row(j, hf)) * LD + 32 * cb + r] = gelu_erf(acc[i][j] + bias);
+      for (int j = 0; j < 16; ++j) {
+          const float hv = acc[i][j] + bias;
+          sm[(32 * (rb0 + i * W / NCB) + mf::d_row(j, hf)) * LD + 32 * cb + r] = hv * normal_cdf(hv);
+        }
   }
   __syncthreads();
   // second layer: wave w serves tokens 16 w .. 16 w + 15, sixteen features per pass
-  const int l16 = lane % 16, q = lane / 16;
-  for (int c0 = 0; c0 < g.dphi; c0 += 16) {
+  const float* ap = sm + (16 * wave + l16) * LD + q;
+  auto put = [&](int a, const f32x4& u) {
+    if (a >= g.dphi) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = 16 * wave + 4 * q + i;
+      if (t < nt) feat[g.th(b, h, t0 + t) * g.nfeat + m * g.dphi + a] = fmaxf(u[i], 0.0f);
+    }
+  };
+  f32x4 u = {b2v, b2v, b2v, b2v};
+#pragma unroll
+  for (int s = 0; s < D / 4; ++s) u = mfma16(ap[4 * s], l16 < g.dphi ? w2v[s] : 0.0f, u);
+  put(l16, u);
+  for (int c0 = 16; c0 < g.dphi; c0 += 16) {
     const int a = c0 + l16;
     const bool live = a < g.dphi;
     const float b2 = live ? c.w.b2[mh * g.dphi + a] : 0.0f;
-    f32x4 u = {b2, b2, b2, b2};
-    const float* ap = sm + (16 * wave + l16) * LD + q;
-    const float* bp = W2 + q * g.dphi + (live ? a : 0);
+    u = f32x4{b2, b2, b2, b2};
+    const float* wp = W2 + q * g.dphi + (live ? a : 0);
 #pragma unroll 8
     for (int s = 0; s < D / 4; ++s) {
-      const float bv = bp[4 * s * g.dphi];
-      u = mfma16(ap[4 * s], live ? bv : 0.0f, u);
+      const float wv = wp[4 * s * g.dphi];
+      u = mfma16(ap[4 * s], live ? wv : 0.0f, u);
     }
-    if (live) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = 16 * wave + 4 * q + i;
-        if (t < nt) feat[g.th(b, h, t0 + t) * g.nfeat + m * g.dphi + a] = fmaxf(u[i], 0.0f);
-      }
-    }
+    put(a, u);
   }
 }
 
@@ -228,25 +270,22 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
         for (int i = 0; i < TPW; ++i) hid[i] = dg[i] = zero16();
         // k-slot (step 4 k4 + j, half hf) is input channel (D / 2) hf + 4 k4 + j
         const float* bp = W1 + (D / 2) * hf * D + 32 * cb + r;
-        float bv[8], bn[8];
+        float bv[8];
+        auto load = [&](int s, float (&v)[8]) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) bv[s] = bp[s * D];
-#pragma unroll 1
-        for (int s0 = 0; s0 < D / 2; s0 += 8) {
-          const int sn = s0 + 8 < D / 2 ? s0 + 8 : s0;
-#pragma unroll
-          for (int s = 0; s < 8; ++s) bn[s] = bp[(sn + s) * D];
+          for (int t = 0; t < 8; ++t) v[t] = bp[(s + t) * D];
+        };
+        load(0, bv);
+        weight_steps<8, D / 2>(bv, load, [&](int s, const float (&v)[8]) {
 #pragma unroll
           for (int s4 = 0; s4 < 8; s4 += 4)
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-              const f32x4 a = *reinterpret_cast<const f32x4*>(xs + (32 * (rb0 + i * W / NCB) + r) * LD + (D / 2) * hf + s0 + s4);
+              const f32x4 a = *reinterpret_cast<const f32x4*>(xs + (32 * (rb0 + i * W / NCB) + r) * LD + (D / 2) * hf + s + s4);
 #pragma unroll
-              for (int j = 0; j < 4; ++j) hid[i] = mfma32(a[j], bv[s4 + j], hid[i]);
+              for (int j = 0; j < 4; ++j) hid[i] = mfma32(a[j], v[s4 + j], hid[i]);
             }
-#pragma unroll
-          for (int s = 0; s < 8; ++s) bv[s] = bn[s];
-        }
+        });
         for (int s = 0; s < (dphi + 1) / 2; ++s) {
           const int a = 2 * s + hf;
           const float w2 = a < dphi ? W2[(32 * cb + r) * dphi + a] : 0.0f;
@@ -259,8 +298,8 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const float hv = hid[i][j] + bias;
-            const float cdf = 0.5f * (1.0f + erff(hv * 0.70710678118654752440f));
-            const float pdf = 0.39894228040143267794f * expf(-0.5f * hv * hv);
+            const float cdf = normal_cdf(hv);
+            const float pdf = 0.39894228040143267794f * __builtin_amdgcn_exp2f(-0.72134752044448170368f * hv * hv);
             const float dh = dg[i][j] * (cdf + hv * pdf);
             const int at = (32 * (rb0 + i * W / NCB) + mf::d_row(j, hf)) * LD + 32 * cb + r;
             dhs[at] = dh;
@@ -273,25 +312,22 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
       __syncthreads();
       if (busy) {
         const float* bp = W1T + (D / 2) * hf * D + 32 * cb + r;
-        float bv[8], bn[8];
+        float bv[8];
+        auto load = [&](int s, float (&v)[8]) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) bv[s] = bp[s * D];
-#pragma unroll 1
-        for (int s0 = 0; s0 < D / 2; s0 += 8) {
-          const int sn = s0 + 8 < D / 2 ? s0 + 8 : s0;
-#pragma unroll
-          for (int s = 0; s < 8; ++s) bn[s] = bp[(sn + s) * D];
+          for (int t = 0; t < 8; ++t) v[t] = bp[(s + t) * D];
+        };
+        load(0, bv);
+        weight_steps<8, D / 2>(bv, load, [&](int s, const float (&v)[8]) {
 #pragma unroll
           for (int s4 = 0; s4 < 8; s4 += 4)
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
-              const f32x4 a = *reinterpret_cast<const f32x4*>(dhs + (32 * (rb0 + i * W / NCB) + r) * LD + (D / 2) * hf + s0 + s4);
+              const f32x4 a = *reinterpret_cast<const f32x4*>(dhs + (32 * (rb0 + i * W / NCB) + r) * LD + (D / 2) * hf + s + s4);
 #pragma unroll
-              for (int j = 0; j < 4; ++j) dx[i] = mfma32(a[j], bv[s4 + j], dx[i]);
+              for (int j = 0; j < 4; ++j) dx[i] = mfma32(a[j], v[s4 + j], dx[i]);
             }
-#pragma unroll
-          for (int s = 0; s < 8; ++s) bv[s] = bn[s];
-        }
+        });
       }
       if constexpr (NM > 0) {
 #pragma unroll
@@ -380,9 +416,11 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
   }
 }
 
-// grid (workgroups per tile list, 1 or H, 2), block W * 64; z = 0: the key maps, z = 1: the query map
+// grid (workgroups per tile list, 1 or H, 2), block W * 64; z = 0: the key maps, z = 1: the query map.
+// Two waves per SIMD: with 260 registers instead of 256 the d = 64 form takes 171 us, not 86 (at 12 heads x
+// 4095 tokens, weight gradients included).
 template <int D, int NM>
-__global__ __launch_bounds__((BwdCfg<D, NM>::THREADS)) void k_f32_phi_bwd(PhiCall c, View Q, View K,
+__global__ __launch_bounds__((BwdCfg<D, NM>::THREADS), 2) void k_f32_phi_bwd(PhiCall c, View Q, View K,
                                                                          const float* __restrict__ feat,
                                                                          const float* __restrict__ dfeat, View dQ,
                                                                          View dK, float* __restrict__ partial) {

@@ -84,3 +84,28 @@ def test_feature_map_tile_edges(F, dphi, d, B, H, N):
         return
     pu.assert_parity(gpu, ref, 1e-4, what)
     pu.assert_weight_grad_parity(gpu["wg"], ref["wg"], 1e-4, what)
+
+
+@pytest.mark.parametrize("d", [32, 128])
+def test_gelu_over_its_range(d):
+    """Maps with W1 = 1, W2 = the first six hidden units, b2 = 0.25 (GELU is above -0.17): the features are
+    GELU(q) + 0.25.  GELU is within 3.9e-7 of the exact one over [-9, 9], the sum adds half an ulp of at most
+    9.25 (4.8e-7); beyond, the negative side must be zero and the positive the identity."""
+    F, dphi, H, N = 3, 6, 1, 3000
+    q = torch.zeros(1, H, N, d)
+    q[0, 0, :, :dphi] = torch.linspace(-9, 9, N * dphi).reshape(N, dphi)
+    q[0, 0, 0, :dphi] = torch.tensor([-10.0, -30.0, -1e4, 12.0, 1e4, 0.0])
+    eye = torch.eye(d, device="cuda")
+    phi = {"W1": eye, "b1": torch.zeros(d, device="cuda"), "W2": eye[:, :dphi].contiguous(), "b2": torch.full((dphi,), 0.25, device="cuda")}
+    op = hla.HLA(head_dim=d, feature_dim=dphi, degree=F, io_dtype=hla.HLA_F32, max_heads=H, max_tokens=N, max_seqs=1)
+    op.set_phi_weights([phi] * (1 + F))
+    qd = q.cuda()
+    op.forward(qd, qd, qd, torch.empty_like(qd))
+    nfeat = (1 + F) * dphi
+    got = torch.as_tensor(op.read_workspace(hla.binding.HLA_WS_FEATURES, N * nfeat)).reshape(N, 1 + F, dphi).double()
+    x = q[0, 0, :, :dphi].double()
+    ref = 0.5 * x * torch.special.erfc(-x / 2 ** 0.5) + 0.25
+    for m in range(1 + F):
+        err = (got[:, m] - ref).abs()
+        assert err[1:].max() < 9e-7, err[1:].max()
+        assert (err[0] <= ref[0].abs() * 6e-8).all(), err[0]
