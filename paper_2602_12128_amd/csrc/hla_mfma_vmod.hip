@@ -797,8 +797,9 @@ __global__ __launch_bounds__(256) void k_vmod_gb_reduce(const float* __restrict_
 // with one partial: [dW1 (in, hidden) | dW2 transposed (out, hidden) | db1 | db2] floats.
 // With the backward writing dU, dH and G and a kernel that contracted them from memory (each array read
 // twice), a map cost 242 us in the backward, and the contractions and their sums 214 + 22 us, at 12 heads
-// x 32760 tokens x 128 channels; now 203 a map, 188 + 7.  No unit is busy more than half of the time: a
+// x 32760 tokens x 128 channels; now 193 a map, 188 + 7.  No unit is busy more than half of the time: a
 // wave's LDS reads, matrix chain, GELU and second chain follow each other, and two waves share a SIMD.
+// Bringing the tiles in by the waves of one role only (the other then has registers to spare): 206.
 template <int D>
 struct VWgSmem {
   static constexpr int kTok = 64;
@@ -1103,7 +1104,9 @@ template <int D, int MAP>
 hla_status backward_map_t(hla_handle* hd, const hla_call_args& a, View out) {
   const Geom& g = hd->g;
   const int64_t tiles = static_cast<int64_t>((g.N + 31) / 32) * g.B * g.H;
-  const int grid = static_cast<int>(std::min<int64_t>(2 * compute_units(), (tiles + kWavesV - 1) / kWavesV));
+  // two workgroups share a compute unit, but not of the form that also adds up dgamma and dbeta: one round
+  // of those (two rounds start and sum twice: 203 us a map at 12 heads x 32760 tokens x 128 channels, now 193)
+  const int grid = static_cast<int>(std::min<int64_t>((hd->vmod_wg_on ? 1 : 2) * compute_units(), (tiles + kWavesV - 1) / kWavesV));
   const unsigned char* saved = hd->vmod_wpk + vmod_mfma_packed_bytes(hd);
   const char* name = MAP == 0 ? "vmod_backward" : "vmod_backward_value";
   if (hd->vmod_wg_on) {
