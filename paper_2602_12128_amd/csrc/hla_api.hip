@@ -119,22 +119,25 @@ namespace {
 
 // Where a handle's device workspace comes from: hipMalloc (one allocation per array, owned by the
 // handle), or consecutive 256-byte aligned pieces of a block of device memory that is not the
-// handle's (base != nullptr; nothing is allocated and nothing will be freed).
+// handle's (base != nullptr; nothing is allocated and nothing will be freed).  measure: only `used`,
+// what such a block has to hold, is added up; the pointers stay null.
 struct Arena {
   unsigned char* base = nullptr;
   size_t cap = 0;
   size_t used = 0;
+  bool measure = false;
   template <typename T>
   hla_status alloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
     const size_t bytes = count * sizeof(T);
-    if (base == nullptr)
+    if (base == nullptr && !measure)
       return hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess ? HLA_OK : HLA_ERR_ALLOC;
     const size_t at = (used + 255) / 256 * 256;
-    if (at + bytes > cap) return HLA_ERR_TOO_LARGE;
-    *p = reinterpret_cast<T*>(base + at);
     used = at + bytes;
+    if (measure) return HLA_OK;
+    if (used > cap) return HLA_ERR_TOO_LARGE;
+    *p = reinterpret_cast<T*>(base + at);
     return HLA_OK;
   }
 };
@@ -284,9 +287,34 @@ hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only) {
   return HLA_OK;
 }
 
+// Plan of the static forward for the exact sizes in `c`.  The generic path's partial states are a matter of
+// speed above one per (sequence, head): where all of them would not fit, as many as do.
+hla_status plan_static(hla_handle* hd, const hla_config& c) {
+  HLA_TRY(plan_handle(hd, c));
+  if (hd->path != HLA_PATH_GENERIC) return HLA_OK;
+  Arena arena;
+  arena.measure = true;
+  HLA_TRY(allocate_workspace(hd, arena, /*forward_only=*/true));
+  if (arena.used <= HLA_STATIC_SCRATCH_BYTES) return HLA_OK;
+  // whole chunks, and what the alignment of the arrays behind the partial states can take back
+  const int64_t over = static_cast<int64_t>(arena.used - HLA_STATIC_SCRATCH_BYTES) + 1024;
+  const int64_t chunk = static_cast<int64_t>(c.max_heads) * hd->state_stride * 4;
+  hd->max_chunks = std::max<int64_t>(hd->max_chunks - (over + chunk - 1) / chunk, c.max_seqs);
+  return HLA_OK;
+}
+
 bool bad_view(const hla_tensor& t) { return t.ptr == nullptr; }
 
 }  // namespace
+
+int64_t hla::static_partial_chunks(const hla_config& cfg, int32_t B, int32_t H, int32_t N) {
+  hla_config c = cfg;
+  c.max_heads = H;
+  c.max_tokens = static_cast<int64_t>(B) * N;
+  c.max_seqs = B;
+  hla_handle plan{};
+  return plan_static(&plan, c) == HLA_OK ? plan.max_chunks : c.max_seqs;
+}
 
 extern "C" {
 
@@ -646,7 +674,7 @@ hla_status hla_forward_static(const hla_config* config, int32_t B, int32_t H, in
     sl.planned = false;
     *hd = hla_handle();
     hd->borrowed_ws = true;
-    HLA_TRY(plan_handle(hd, c));
+    HLA_TRY(plan_static(hd, c));
     Arena arena;
     arena.base = sl.ptr;
     arena.cap = HLA_STATIC_SCRATCH_BYTES;

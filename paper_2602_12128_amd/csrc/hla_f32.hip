@@ -22,6 +22,9 @@ namespace {
 using namespace f32;
 using mf::static_for;
 
+// four floats on a 4-byte address: a state is nm (d + 1) floats, and they follow each other without gaps
+typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
+
 // ---- forms --------------------------------------------------------------------------------------
 // The paper's two forms with everything about their monomials known at compile time, and the
 // run-time form (tables below) for every other (F, d_phi).
@@ -51,7 +54,7 @@ struct MonoTable {
 };
 
 struct F32Geom {
-  int64_t stride;   // floats of one state: [32 mpb][d] rows, then z [32 mpb]
+  int64_t stride;   // floats of one state: [nm][d] rows, then z [nm]
   int nm, mpb;      // monomials, row blocks
   int F, dphi, D;   // D = d_phi^F
   int io_bf16;      // caller's tensors are bf16 (else fp32)
@@ -210,9 +213,10 @@ __device__ __forceinline__ void accumulate_state(int mpb, const float* mt, const
   }
 }
 
-// out[m][t] = sum_c C[m][c] rows[t][c] into xt[m][LT] (rows of C from LDS or, run-time form, from memory)
+// out[m][t] = sum_c C[m][c] rows[t][c] into xt[m][LT] (rows of C from LDS or, run-time form, from memory:
+// the last one stands in for those past it, whose products nobody reads)
 template <class FM, int D, int W, int LT>
-__device__ __forceinline__ void rows_times_state(int mpb, const float* C, const float* rows, int wave, int lane,
+__device__ __forceinline__ void rows_times_state(int nm, int mpb, const float* C, const float* rows, int wave, int lane,
                                                  float* xt) {
   constexpr int LD = D + 4, TB = FM::TOK / 32, LC = FM::kRt ? D : LD;
   constexpr int TPW = (FM::MPB * TB + W - 1) / W;
@@ -222,12 +226,13 @@ __device__ __forceinline__ void rows_times_state(int mpb, const float* C, const 
     const int tile = wave + W * i;
     if (tile < mpb * TB) {
       const int mb = tile % mpb, tb = tile / mpb;
-      const float* ap = C + static_cast<int64_t>(32 * mb + r) * LC + (D / 2) * hf;
+      const int row = FM::kRt ? min(32 * mb + r, nm - 1) : 32 * mb + r;
+      const float* ap = C + static_cast<int64_t>(row) * LC + (D / 2) * hf;
       const float* bp = rows + (32 * tb + r) * LD + (D / 2) * hf;
       f32x16 acc = zero16();
 #pragma unroll
       for (int k4 = 0; k4 < D / 8; ++k4) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(ap + 4 * k4);
+        const f32x4 a = *reinterpret_cast<const std::conditional_t<FM::kRt, f32x4_dw, f32x4>*>(ap + 4 * k4);
         const f32x4 b = *reinterpret_cast<const f32x4*>(bp + 4 * k4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc = mfma32(a[j], b[j], acc);
@@ -285,7 +290,7 @@ template <class FM, int D, int THREADS>
 __device__ __forceinline__ void stage_state(const float* __restrict__ st, float* cs) {
   constexpr int P = D / 4;
   for (int i = threadIdx.x; i < FM::NM * P; i += THREADS)
-    *reinterpret_cast<f32x4*>(cs + (i / P) * (D + 4) + 4 * (i % P)) = *reinterpret_cast<const f32x4*>(st + 4 * i);
+    *reinterpret_cast<f32x4*>(cs + (i / P) * (D + 4) + 4 * (i % P)) = *reinterpret_cast<const f32x4_dw*>(st + 4 * i);
 }
 
 template <class FM, int D>
@@ -318,7 +323,7 @@ __device__ __forceinline__ void accumulate_z(int rows, const float* mt, const fl
     }
   }
 }
-// accumulators and z to one partial state ([rows][D], then z); red: W * 64 * NZ floats of LDS
+// accumulators and z to one partial state ([nm][D], then z [nm]); red: W * 64 * NZ floats of LDS
 template <class FM, int D>
 __device__ __forceinline__ void store_partial(int nm, int mpb, const f32x16 (&acc)[Cfg<FM, D>::TPW],
                                               const float (&z)[Cfg<FM, D>::NZ], float* red, float* __restrict__ out) {
@@ -344,7 +349,7 @@ __device__ __forceinline__ void store_partial(int nm, int mpb, const f32x16 (&ac
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < CF::W; ++w) s += red[(w * CF::NZ + m / 64) * 64 + m % 64];
-    out[32 * mpb * D + m] = s;
+    out[nm * D + m] = s;
   }
 }
 
@@ -462,7 +467,7 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_query(Geom g, F32
   const BlockEnt e = runs[blockIdx.x];
   const int h = blockIdx.y, lane = threadIdx.x % 64, wave = mf::wave_index();
   const float* st = state + (static_cast<int64_t>(e.seq) * g.H + h) * x.stride;
-  const float* zv = st + 32 * mpb * D;
+  const float* zv = st + nm * D;
   if constexpr (!FM::kRt) stage_state<FM, D, CF::THREADS>(st, cs);
   if (FM::kRt && (nm & 1)) {
     if (threadIdx.x < CF::TOK) mt[nm * CF::LT + threadIdx.x] = 0.0f;
@@ -521,7 +526,7 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_bwd_query(
   const BlockEnt e = runs[blockIdx.x];
   const int h = blockIdx.y, lane = threadIdx.x % 64, wave = mf::wave_index();
   const float* st = state + (static_cast<int64_t>(e.seq) * g.H + h) * x.stride;
-  const float* zv = st + 32 * mpb * D;
+  const float* zv = st + nm * D;
   if constexpr (!FM::kRt) stage_state<FM, D, CF::THREADS>(st, cs);
   f32x16 acc[CF::TPW];
   float z[CF::NZ];
@@ -538,7 +543,7 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_bwd_query(
     __syncthreads();
     const float inv = invs[lane % CF::TOK];
     tile_monomials<FM, true, CF::W, CF::LT>(x, fs, dp | 1, wave, lane, inv, mt);
-    rows_times_state<FM, D, CF::W, CF::LT>(mpb, FM::kRt ? st : cs, gs, wave, lane, xt);
+    rows_times_state<FM, D, CF::W, CF::LT>(nm, mpb, FM::kRt ? st : cs, gs, wave, lane, xt);
     __syncthreads();
     {
       const int t = threadIdx.x % CF::TOK, part = threadIdx.x / CF::TOK;
@@ -627,7 +632,7 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_bwd_key(Geom g, F
   const BlockEnt e = runs[blockIdx.x];
   const int h = blockIdx.y, lane = threadIdx.x % 64, wave = mf::wave_index();
   const float* st = dstate + (static_cast<int64_t>(e.seq) * g.H + h) * x.stride;
-  const float* zv = st + 32 * mpb * D;
+  const float* zv = st + nm * D;
   if constexpr (!FM::kRt) stage_state<FM, D, CF::THREADS>(st, cs);
   if (FM::kRt && (nm & 1)) {
     if (threadIdx.x < CF::TOK) mt[nm * CF::LT + threadIdx.x] = 0.0f;
@@ -639,7 +644,7 @@ __global__ __launch_bounds__((Cfg<FM, D>::THREADS)) void k_f32_bwd_key(Geom g, F
     stage_features<CF::TOK, CF::THREADS>(feat, th0, g.nfeat, dp, nk, nt, nk | 1, fs);
     __syncthreads();
     tile_monomials<FM, false, CF::W, CF::LT>(x, fs, nk | 1, wave, lane, 1.0f, mt);
-    rows_times_state<FM, D, CF::W, CF::LT>(mpb, FM::kRt ? st : cs, vs, wave, lane, xt);
+    rows_times_state<FM, D, CF::W, CF::LT>(nm, mpb, FM::kRt ? st : cs, vs, wave, lane, xt);
     __syncthreads();
     if constexpr (!FM::kRt) {
       constexpr int MQ = Part<FM, CF::W>::MQ, NM = FM::NM, DP = FM::DP, F = FM::F;
@@ -716,7 +721,7 @@ F32Geom f32_geom(const hla_handle* hd) {
   x.D = hd->g.D;
   x.nm = static_cast<int>(binomial(x.dphi + x.F - 1, x.F));
   x.mpb = (x.nm + 31) / 32;
-  x.stride = static_cast<int64_t>(32) * x.mpb * (hd->g.d + 1);
+  x.stride = static_cast<int64_t>(x.nm) * (hd->g.d + 1);
   x.io_bf16 = hd->cfg.io_dtype == HLA_BF16;
   x.tab = static_cast<const MonoTable*>(hd->path_ws);
   return x;
@@ -729,9 +734,9 @@ int tok_of(const hla_handle* hd) { return is_rt(hd) ? FormRt::TOK : 64; }
 // Runs of tokens per (sequence, head): enough workgroups for two per compute unit, never more
 // partial states than the workspace holds (but at least one run per sequence).
 int64_t max_partials(const hla_handle* hd) {
-  // 8 MiB of partial states: 504 workgroups for the three-factor form at d = 64, 254 (of eight waves)
-  // at d = 128; more would only add to what the reduction reads
-  const int64_t fit = (8ll << 20) / (hd->state_stride * 4);
+  // 504 workgroups for the three-factor form at d = 64, 254 (of eight waves) at d = 128: 8 MiB of partial
+  // states with their rows counted in whole tiles; more would only add to what the reduction reads
+  const int64_t fit = (8ll << 20) / (static_cast<int64_t>(128) * f32_geom(hd).mpb * (hd->g.d + 1));
   return std::min<int64_t>(512, std::max<int64_t>(fit, 16));
 }
 
@@ -756,8 +761,11 @@ hla_status allow_lds(const F32Geom& x) {
 
 hla_status runs_table(hla_handle* hd, const hla_call_args& a, hla_token_table** out) {
   const int tok = tok_of(hd);
-  const int64_t cap = max_partials(hd);
   const int nseq = a.num_seqs;
+  int64_t cap = max_partials(hd);
+  // a call that the static forward also takes cuts its tokens into the same runs there: same bits
+  if (hd->cfg.phi_mode == HLA_PHI_NONE && !a.packed)
+    cap = std::min(cap, static_partial_chunks(hd->cfg, a.B, a.H, a.N) * a.H);
   auto count = [&](int64_t per) {  // runs per head with `per` tiles each
     const int64_t blk = per * tok;
     if (!a.packed) return static_cast<int64_t>(a.B) * ((a.N + blk - 1) / blk);

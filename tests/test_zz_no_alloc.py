@@ -62,6 +62,24 @@ def test_static_forward_reads_features_in_place(F, dphi, d):
             assert torch.equal(O.cpu(), want), (N, pad, off)
 
 
+@pytest.mark.parametrize("F,dphi,d,H,N", [
+    (2, 12, 64, 12, 14565),
+    (2, 12, 32, 12, 16426),
+    (1, 6, 128, 12, 50349),
+    (1, 256, 128, 1, 15200),   # room for 16 of 63 partial states
+    (3, 5, 64, 12, 23541),     # an odd number of monomials: states on 4-byte addresses
+])
+def test_static_forward_takes_calls_that_fill_the_array(F, dphi, d, H, N):
+    """fp32 calls that fit the static array with as many partial states as the sequence has thousands of
+    tokens: what the kernels would like beyond that gives way, in the handle's forward of that shape too."""
+    t = wl.make_feature_inputs(980 + F, 1, H, N, d, F, dphi, torch.float32)
+    got = _static_forward(t, F, dphi, io_dtype=hla.HLA_F32)
+    want = pu.run_gpu(t, F, dphi, 1e-6, backward=False)
+    assert torch.equal(got, want["O"])
+    ref = pu.run_oracle(t, F, dphi, 1e-6, backward=False)
+    pu.assert_parity({"O": got}, ref, 1e-4, f"static forward F={F} d_phi={dphi} d={d} N={N}")
+
+
 def test_static_forward_limits():
     dev = torch.device("cuda:0")
     # a layout that does not fit the static array is refused and leaves the output alone
