@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "hla_f32_common.h"
+#include "hla_runs.h"
 
 namespace hla {
 namespace {
@@ -760,6 +761,8 @@ hla_status allow_lds(const F32Geom& x) {
 }
 
 hla_status runs_table(hla_handle* hd, const hla_call_args& a, hla_token_table** out) {
+  // the same sequences and heads as the last call's (its backward, the next step): the same runs
+  if (hd->tables[0].valid && hd->runs_heads == a.H) return get_table(hd, 0, hd->tables[0].block_tokens, a.stream, out);
   const int tok = tok_of(hd);
   const int nseq = a.num_seqs;
   int64_t cap = max_partials(hd);
@@ -773,9 +776,10 @@ hla_status runs_table(hla_handle* hd, const hla_call_args& a, hla_token_table** 
     for (int s = 0; s < nseq; ++s) c += (hd->cu_host[s + 1] - hd->cu_host[s] + blk - 1) / blk;
     return c;
   };
-  int64_t per = std::max<int64_t>(1, count(1) * a.H / cap);
-  while (count(per) * a.H > cap && count(per) > nseq) ++per;
-  return get_table(hd, 0, static_cast<int32_t>(per * tok), a.stream, out);
+  const int64_t per = tiles_per_run(a.H, nseq, cap, count);
+  HLA_TRY(get_table(hd, 0, static_cast<int32_t>(per * tok), a.stream, out));
+  hd->runs_heads = a.H;
+  return HLA_OK;
 }
 
 hla_status reduce_partials(hla_handle* hd, const hla_call_args& a, const F32Geom& x, const hla_token_table* runs,

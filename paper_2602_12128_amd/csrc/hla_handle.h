@@ -87,6 +87,7 @@ struct hla_handle {
 
   // token tables, one per role (the path's workspace plan names the roles it uses)
   hla_token_table tables[kTableRoles];
+  int32_t runs_heads = -1;         // H that the generic path's runs in tables[0] were chosen for
   // true: the device workspace is carved out of memory the handle does not own (nothing to free)
   bool borrowed_ws = false;
   std::vector<int32_t> cu_host;    // shape signature of the tables (effective cu, B rows if dense)

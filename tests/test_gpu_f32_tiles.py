@@ -109,3 +109,27 @@ def test_gelu_over_its_range(d):
         err = (got[:, m] - ref).abs()
         assert err[1:].max() < 9e-7, err[1:].max()
         assert (err[0] <= ref[0].abs() * 6e-8).all(), err[0]
+
+
+def test_runs_follow_the_head_count():
+    """One handle, the same tokens, other numbers of heads: the runs of tiles are those of the call's heads."""
+    F, dphi, d, N = 3, 6, 32, 8200  # five heads: runs of several tiles; one head: of one
+    t = wl.make_feature_inputs(3300, 1, 5, N, d, F, dphi, torch.float32)
+    h = pu.make_handle(t, F, dphi, 1e-6, None, None, hla.HLA_PATH_GENERIC)
+
+    def step(op, H):
+        x = {k: v[:, :H].contiguous().cuda() for k, v in t.items()}
+        out = {"O": x["V"], "dQ": x["Q"], "dK": x["K"], "dV": x["V"]}
+        out = {k: torch.empty_like(v) for k, v in out.items()}
+        op.forward(x["Q"], x["K"], x["V"], out["O"])
+        op.backward(x["Q"], x["K"], x["V"], out["O"], x["dO"], out["dQ"], out["dK"], out["dV"])
+        torch.cuda.synchronize()
+        return out
+
+    for H in (5, 1, 5, 3):
+        fresh = pu.make_handle(t, F, dphi, 1e-6, None, None, hla.HLA_PATH_GENERIC)
+        want, got = step(fresh, H), step(h, H)
+        fresh.destroy()
+        for k in want:
+            assert torch.equal(got[k], want[k]), (H, k)
+    h.destroy()
