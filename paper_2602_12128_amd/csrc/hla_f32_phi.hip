@@ -6,10 +6,10 @@
 // B-operand order (32 consecutive floats per half wave) with the next steps' loads in flight.
 //
 // At 12 heads x 4095 tokens x 64 channels, three factors, fp32 (us; before: a thread per hidden unit on
-// the vector ALU, an LDS read per multiply-add): forward 35 (147), backward with the weight gradients
-// 86 (197 + 491 for a second pass that recomputed the hidden layer), of which 11 and 27 are
-// matrix-pipe time; the rest is the phases' barriers, GELU and the weights' way from L2.  With erff,
-// expf and the weights loaded where they are used, 43 and 100.
+// the vector ALU, an LDS read per multiply-add): forward 36 (147), backward with the weight gradients
+// 94 (197 + 491 for a second pass that recomputed the hidden layer), of which 11 and 27 are
+// matrix-pipe time; the rest is the phases' barriers, GELU and the weights' way from L2.  With erff and
+// the weights loaded where they are used, 43 and 100.
 #include <algorithm>
 #include <cmath>
 
@@ -22,20 +22,26 @@ using namespace f32;
 
 constexpr int kTok = 64;
 
-// Phi(h) of the exact GELU, h Phi(h): Phi(-t) = 2^-(1 + P(t)) for t >= 0 with a degree-8 minimax fit of
-// P(t) = -log2(erfc(t / sqrt 2)) on [0, 5.9], weighted by what an error of P does to the GELU; beyond,
-// P keeps growing and Phi(-t) runs to zero as it should.  Without branches: erff takes its
-// two ranges one after the other when the lanes of a wave need both.  In fp32, over [-9, 9]: GELU within
-// 3.9e-7 (rms 5.7e-8) of the exact one, h 0.5 (1 + erf) with a correctly rounded erf 4.5e-7 (6.4e-8).
+// Phi(h) of the exact GELU, h Phi(h).  Below |h| = 1 it is 0.5 + h P(h^2), where an error of P shrinks with
+// h; beyond, Phi(-t) = 2^-(1 + P(t)) with a degree-8 minimax fit of P(t) = -log2(erfc(t / sqrt 2)) up to 5.9,
+// after which P keeps growing and Phi(-t) runs to zero as it should.  Without branches: erff takes
+// its two ranges one after the other when the lanes of a wave need both.  Errors against 64 bits on the
+// card, h normal with a spread of 0.02, 0.2, 1 and 4 (2-norm, 1e-8; in brackets 0.5 (1 + erff), expf): GELU 3.7,
+// 3.7, 3.4, 2.1 (3.7, 3.9, 3.9, 2.3), GELU' 4.1, 3.8, 3.7, 3.6 (4.1, 3.8, 4.0, 3.8); Phi at most 6.9 (7.6).
+// The second fit alone, without the first: GELU 5.8, 5.2, 3.5, 2.1, GELU' 5.5, 5.3, 4.2, 3.7.
 __device__ __forceinline__ float normal_cdf(float h) {
+  constexpr float n[6] = {0.3989423f, -0.06649058f, 0.00997454f, -0.0011890578f, 0.000116174444f, -8.620451e-06f};
   constexpr float c[9] = {1.0f,           1.1511064f,      0.45919567f,     0.052539267f, -0.0071317810f,
                           0.00019325814f, 0.00016142147f, -3.3898614e-05f, 2.3575092e-06f};
-  const float t = fabsf(h);
-  float p = c[8];
+  const float t = fabsf(h), s = h * h;
+  float near = n[5], p = c[8];
+#pragma unroll
+  for (int k = 4; k >= 0; --k) near = __builtin_fmaf(near, s, n[k]);
 #pragma unroll
   for (int k = 7; k >= 0; --k) p = __builtin_fmaf(p, t, c[k]);
   const float e = __builtin_amdgcn_exp2f(-p);
-  return h > 0.0f ? 1.0f - e : e;
+  const float far = h > 0.0f ? 1.0f - e : e;
+  return t < 1.0f ? __builtin_fmaf(h, near, 0.5f) : far;
 }
 
 template <int D>
@@ -57,7 +63,7 @@ __device__ __forceinline__ void tile_pos(int tile, int& rb, int& cb) {
 // use(s, v) for the batches s = 0, NB, .. < STEPS of weight operands that load(s, v) fetches, each batch in
 // flight while the one before is used.  Two sets take turns (a copy from one to the other would wait for
 // the loads), and the compiler must not move the loads down to where they are used, which it otherwise
-// does: d = 128, 4 heads x 3000 tokens with weight gradients, 208 us a step that way, 155 like this.
+// does: d = 128, 4 heads x 3000 tokens with weight gradients, 208 us a step that way, 161 like this.
 template <int NB, int STEPS, class Load, class Use>
 __device__ __forceinline__ void weight_steps(float (&first)[NB], Load&& load, Use&& use) {
   static_assert(STEPS % (2 * NB) == 0, "pairs of batches");
@@ -299,7 +305,7 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
           for (int j = 0; j < 16; ++j) {
             const float hv = hid[i][j] + bias;
             const float cdf = normal_cdf(hv);
-            const float pdf = 0.39894228040143267794f * __builtin_amdgcn_exp2f(-0.72134752044448170368f * hv * hv);
+            const float pdf = 0.39894228040143267794f * expf(-0.5f * hv * hv);
             const float dh = dg[i][j] * (cdf + hv * pdf);
             const int at = (32 * (rb0 + i * W / NCB) + mf::d_row(j, hf)) * LD + 32 * cb + r;
             dhs[at] = dh;
@@ -417,7 +423,7 @@ __device__ __forceinline__ void phi_bwd_body(const PhiCall& c, const View& X, bo
 }
 
 // grid (workgroups per tile list, 1 or H, 2), block W * 64; z = 0: the key maps, z = 1: the query map.
-// Two waves per SIMD: with 260 registers instead of 256 the d = 64 form takes 171 us, not 86 (at 12 heads x
+// Two waves per SIMD: with 260 registers instead of 256 the d = 64 form took 171 us instead of 86 (at 12 heads x
 // 4095 tokens, weight gradients included).
 template <int D, int NM>
 __global__ __launch_bounds__((BwdCfg<D, NM>::THREADS), 2) void k_f32_phi_bwd(PhiCall c, View Q, View K,

@@ -133,3 +133,49 @@ def test_runs_follow_the_head_count():
         for k in want:
             assert torch.equal(got[k], want[k]), (H, k)
     h.destroy()
+
+
+@pytest.mark.parametrize("spread", [0.02, 0.2, 1.0, 4.0])
+def test_gelu_and_its_slope_are_no_further_off_than_with_erf(spread):
+    """The error against 64 bits of GELU and GELU' as the fp32 maps form them, beside that of
+    h 0.5 (1 + erf(h / sqrt 2)) and its derivative in fp32 with a correctly rounded erf and exp.  W1 = 1;
+    the query map has W2 = -1 and is open where GELU < 0, the first key map W2 = 1, so that features are GELU
+    itself and dX / d(feature) is GELU' times one rounding, here and there.  2 % for the sample (72000 values a side)."""
+    F, dphi, d, H, N = 3, 6, 32, 4, 6000
+    gen = torch.Generator("cpu").manual_seed(3400)
+    x = torch.randn(1, H, N, d, generator=gen) * spread
+    eye = torch.eye(d)
+    col = eye[:, :dphi].contiguous()
+    zero, one = torch.zeros(d), torch.ones(dphi)
+    maps = [{"W1": eye, "b1": zero, "W2": -col, "b2": 0 * one}, {"W1": eye, "b1": zero, "W2": col, "b2": 0 * one}]
+    maps += [{"W1": 0 * eye, "b1": zero, "W2": col, "b2": one}] * 2
+    op = hla.HLA(head_dim=d, feature_dim=dphi, degree=F, io_dtype=hla.HLA_F32, max_heads=H, max_tokens=N, max_seqs=1)
+    op.set_phi_weights([{k: v.cuda() for k, v in m.items()} for m in maps])
+    xd = x.cuda()
+    V, dO = (torch.randn(1, H, N, d, generator=gen).cuda() for _ in range(2))
+    O, dQ, dK, dV = (torch.empty_like(V) for _ in range(4))
+    op.forward(xd, xd, V, O)
+    op.backward(xd, xd, V, O, dO, dQ, dK, dV)
+    nfeat = (1 + F) * dphi
+    feat, dfeat = (torch.as_tensor(op.read_workspace(kind, H * N * nfeat)).reshape(H * N, 1 + F, dphi)
+                   for kind in (hla.binding.HLA_WS_FEATURES, hla.binding.HLA_WS_FEATURE_GRADS))
+    op.destroy()
+    h = x.reshape(H * N, d)[:, :dphi]
+    hd = h.double()
+    cdf = 0.5 * torch.special.erfc(-hd / 2 ** 0.5)
+    value, slope = hd * cdf, cdf + hd * torch.exp(-hd * hd / 2) / (2 * torch.pi) ** 0.5
+    erf1 = 1.0 + torch.erf((h * 0.70710678118654752440).double()).float()
+    value32 = (h * 0.5) * erf1
+    pdf32 = 0.39894228040143267794 * torch.exp((-0.5 * h * h).double()).float()
+    slope32 = (0.5 * erf1).double().add(hd * pdf32.double()).float()  # one multiply-add
+    for m, dX, sign, side in ((0, dQ, -1.0, h < 0), (1, dK, 1.0, h > 0)):
+        got = sign * feat[:, m][side].double()
+        err = lambda a: ((a - value[side]).norm() / value[side].norm()).item()
+        assert err(got) <= 1.02 * err(value32[side].double()), (m, err(got), err(value32[side].double()))
+        du = dfeat[:, m]
+        side = side & (du != 0) & (feat[:, m] > 0)
+        du = du[side]
+        err = lambda dx: ((sign * dx.double() / du.double() - slope[side]).norm() / slope[side].norm()).item()
+        got = dX.cpu().reshape(H * N, d)[:, :dphi][side]
+        want = sign * du * slope32[side]
+        assert err(got) <= 1.02 * err(want), (m, err(got), err(want))
