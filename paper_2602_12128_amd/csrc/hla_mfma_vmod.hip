@@ -167,7 +167,7 @@ struct SavedTile {
 
 // What the backward kernel leaves of map m for the maps' weight gradients when they are asked for: the
 // gradient w.r.t. the second layer's output as the matrix cores see it (fp16 [token-heads][D], a token's
-// row scaled to unit norm) and the scale of each token.  The LayerNorm's dgamma = sum over tokens of
+// row scaled to norm kRowNorm) and the scale of each token.  The LayerNorm's dgamma = sum over tokens of
 // dm * u-hat and dbeta = sum of dm (dm: gradient w.r.t. the map's output) need no array: the kernel adds
 // them up per lane as it goes and leaves one partial per workgroup in gb_part
 // ([workgroup][dgamma | dbeta][D] floats).
@@ -441,9 +441,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_vmod_fwd_mfma(Geom g, const unsi
 // LayerNorm backward of one map for the lane's token, ready for the matrix cores.  With
 // gg = dO * m_other * gamma (m_other = the other map's output) and means over the channels,
 //   du = rstd (gg - mean(gg) - u-hat mean(gg u-hat)).
-// Returns t = (gg - mean(gg) - u-hat mean(gg u-hat)) / |gg|_2 as packed fp16 B operands (k-slot =
-// channel) and the factor rstd |gg|_2 that dx must be multiplied with: scaled to unit Euclidean
-// norm per token, the operand's range does not depend on the size of dO or of 1/std.
+// Returns t = kRowNorm (gg - mean(gg) - u-hat mean(gg u-hat)) / |gg|_2 as packed fp16 B operands (k-slot =
+// channel) and the factor rstd |gg|_2 / kRowNorm that dx must be multiplied with: scaled to one
+// Euclidean norm per token, the operand's range does not depend on the size of dO or of 1/std.  The norm is
+// 1024, so that channels down to 2^-24 of a row's norm are normal fp16 numbers.
+constexpr float kRowNorm = 1024.0f;
 // The row is streamed twice, 16-byte piece by piece (first for the three sums, then for the
 // result), through `load(which, ks, pass)`: piece ks of dO (which = 0, packed bf16), of this map's
 // u-hat (1) and of the other map's (2, both packed fp16).  Only the result stays in registers; the
@@ -512,7 +514,7 @@ __device__ __forceinline__ float norm_backward(const unsigned char* wm_self, con
   sb += partner32(sb);
   sc += partner32(sc);
   const float nrm = sqrtf(sc);
-  const float inv = nrm > 0.0f ? 1.0f / nrm : 0.0f;
+  const float inv = nrm > 0.0f ? kRowNorm / nrm : 0.0f;
   const float a = sa * (1.0f / D) * inv, bq = sb * (1.0f / D) * inv;
   asm volatile("" : "+s"(z2));
   __builtin_amdgcn_sched_barrier(0);
@@ -535,7 +537,7 @@ __device__ __forceinline__ float norm_backward(const unsigned char* wm_self, con
       }
     }
   }
-  return rstd * nrm;
+  return rstd * nrm * (1.0f / kRowNorm);
 }
 
 // dx^T = W1 (GELU'(4y) * (W2 du^T)) for one map: dub = du as fp16 B operands, x = the map's input
@@ -786,13 +788,16 @@ __global__ __launch_bounds__(256) void k_vmod_gb_reduce(const float* __restrict_
 // ---- weight gradients of the two layers ---------------------------------------------------------------
 // With y the first layer's output / 4, t and s what the backward kernel left of a token (see VmodFactors):
 //   dU = s t,  dH = GELU'(4y) * s (t W2^T),  G = GELU(4y):
-//   dW1 = X^T dH, db1 = sum dH, dW2 = G^T dU, db2 = sum dU          (sums over all tokens)
+//   dW1 = X^T dH, db1 = sum dH, dW2 = (s G)^T t, db2 = sum dU       (sums over all tokens)
+// t is contracted as it stands: forming dU in 16 bits would round it a second time.  s G goes into fp16 in
+// units of 2^e, e the exponent of the largest scale a wave has met: the sums are rescaled where a larger one
+// turns up, and a token is rounded to nothing only 2^-24 below it.
 // for map blockIdx.y.  A token is an MFMA row here (as in the feature maps' weight gradients): the
 // hidden layer leaves its unit in a lane and its tokens in the accumulator registers, which is the
 // operand the contractions over tokens want, so dH and G never leave the registers.
 // Waves w and w + 4 share a SIMD and a block of 32 hidden units whose weights they keep in registers;
 // the first forms dH and dW1, the second G and dW2 (both compute the block's first layer).  The 64-token
-// tiles of X, t and bf16 dU are shared by the waves of a group in LDS, two buffers, loaded through
+// tiles of X and t are shared by the waves of a group in LDS, two buffers, loaded through
 // registers a tile ahead; one barrier per tile.  A group (512 threads at D = 128, 256 at D = 64) ends
 // with one partial: [dW1 (in, hidden) | dW2 transposed (out, hidden) | db1 | db2] floats.
 // With the backward writing dU, dH and G and a kernel that contracted them from memory (each array read
@@ -804,7 +809,7 @@ template <int D>
 struct VWgSmem {
   static constexpr int kTok = 64;
   static constexpr int kRows = kTok * D * 2;                   // one tile of one array
-  static constexpr int kScale = 3 * kRows;                     // X, t, dU, then the tokens' scales
+  static constexpr int kScale = 2 * kRows;                     // X, t, then the tokens' scales
   static constexpr int kBuf = kScale + kTok * 4;
   static constexpr int kGroups = 128 / D;
   static constexpr int kTotal = kGroups * 2 * kBuf;
@@ -866,21 +871,18 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
     for (int k = 0; k < 2; ++k) {
       const int t = tok + 32 * k, at = tile_off<D * 2>(t, piece);
       const bool live = tile < total && n0 + t < g.N;
-      u32x4 tv = tr[k], u;
+      u32x4 tv = tr[k];
       const float sv = live ? sr[k] : 0.0f;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         if (!live) tv[p] = 0u;
         const uint32_t w = tv[p];
         const f16x2 t2 = __builtin_bit_cast(f16x2, w);
-        const float u0 = static_cast<float>(t2[0]) * sv, u1 = static_cast<float>(t2[1]) * sv;
-        db2[2 * p] += u0;
-        db2[2 * p + 1] += u1;
-        u[p] = pack_bf16(u0, u1);
+        db2[2 * p] += static_cast<float>(t2[0]) * sv;
+        db2[2 * p + 1] += static_cast<float>(t2[1]) * sv;
       }
       *reinterpret_cast<u32x4*>(buf + at) = xr[k];
       *reinterpret_cast<u32x4*>(buf + SM::kRows + at) = tv;
-      *reinterpret_cast<u32x4*>(buf + 2 * SM::kRows + at) = u;
       if (piece == 0) *reinterpret_cast<float*>(buf + SM::kScale + t * 4) = sv;
     }
   };
@@ -902,8 +904,9 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
   for (int ib = 0; ib < NRB; ++ib)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[ib][i] = 0.0f;
-  // acc += (rows of `tile` transposed) * v over the 32 tokens of a sub-tile
-  auto contract = [&](const unsigned char* tile, const u32x4 (&v)[2]) {
+  int e2 = -1000;  // role 1: the sums are in units of 2^e2
+  // acc += (rows of `tile` transposed) * v over the 32 tokens of a sub-tile, bf16 (X, dH) or fp16 (t, s G)
+  auto contract = [&](auto BF16, const unsigned char* tile, const u32x4 (&v)[2]) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       u32x4 a[NRB];
@@ -917,7 +920,8 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
         a[ib][3] = hi[1];
       }
 #pragma unroll
-      for (int ib = 0; ib < NRB; ++ib) acc[ib] = mfma32(a[ib], v[ks], acc[ib]);
+      for (int ib = 0; ib < NRB; ++ib)
+        acc[ib] = BF16.value ? mfma32(a[ib], v[ks], acc[ib]) : mfma32_f16(a[ib], v[ks], acc[ib]);
     }
   };
   auto first_layer = [&](const unsigned char* xs) {
@@ -947,7 +951,11 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
       for (int sub = 0; sub < 2; ++sub) {
         const unsigned char* xs = buf + sub * 32 * D * 2;
         const unsigned char* ts = xs + SM::kRows;
-        const unsigned char* us = xs + 2 * SM::kRows;
+        f32x4 sc[4];  // of tokens 8 i + 4 gl + 0 .. 3
+        auto scales = [&]() {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[i] = *reinterpret_cast<const f32x4*>(buf + SM::kScale + (32 * sub + 8 * i + 4 * gl) * 4);
+        };
         u32x4 v[2];
         if constexpr (DH.value) {
           f32x16 dg;
@@ -958,9 +966,7 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
           asm volatile("" : "+v"(dg) : : "memory");  // the first layer's operands are read after this: registers are short
           const f32x16 y = first_layer(xs);
           __builtin_amdgcn_sched_barrier(0);
-          f32x4 sc[4];  // of tokens 8 i + 4 gl + 0 .. 3
-#pragma unroll
-          for (int i = 0; i < 4; ++i) sc[i] = *reinterpret_cast<const f32x4*>(buf + SM::kScale + (32 * sub + 8 * i + 4 * gl) * 4);
+          scales();
           f16x2 yh[8], gp[8];
 #pragma unroll
           for (int p = 0; p < 8; ++p) yh[p] = to_f16x2(y[2 * p], y[2 * p + 1]);
@@ -972,7 +978,7 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
             db1 += d0 + d1;
             v[p / 4][p % 4] = pack_bf16(d0, d1);
           }
-          contract(xs, v);
+          contract(DH, xs, v);
         } else {
           const f32x16 y = first_layer(xs);
           f16x2 yh[8];
@@ -980,12 +986,27 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
 #pragma unroll
           for (int p = 0; p < 8; ++p) yh[p] = to_f16x2(y[2 * p], y[2 * p + 1]);
           gelu_y16<8>(yh, gq);
+          scales();
+          float top = 0.0f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) top = fmaxf(top, sc[i / 4][i % 4]);
+          top = fmaxf(top, partner32(top));
+          const int et = __builtin_amdgcn_readfirstlane(top > 0.0f ? __builtin_amdgcn_frexp_expf(top) : e2);
+          if (et > e2) {
+#pragma unroll
+            for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) acc[ib][i] = __builtin_amdgcn_ldexpf(acc[ib][i], e2 - et);
+            e2 = et;
+          }
 #pragma unroll
           for (int p = 0; p < 8; ++p) {
             const f16x2 g2 = __builtin_bit_cast(f16x2, gq[p]);
-            v[p / 4][p % 4] = pack_bf16(static_cast<float>(g2[0]), static_cast<float>(g2[1]));
+            const float s0 = __builtin_amdgcn_ldexpf(sc[p / 2][2 * (p % 2)], -e2);
+            const float s1 = __builtin_amdgcn_ldexpf(sc[p / 2][2 * (p % 2) + 1], -e2);
+            v[p / 4][p % 4] = __builtin_bit_cast(uint32_t, to_f16x2(static_cast<float>(g2[0]) * s0, static_cast<float>(g2[1]) * s1));
           }
-          contract(us, v);
+          contract(DH, ts, v);
         }
       }
       // the buffer of the tile before this one, which every wave left before the last barrier
@@ -1002,7 +1023,8 @@ __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned ch
 #pragma unroll
   for (int ib = 0; ib < NRB; ++ib)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) out[role * D * D + (32 * ib + d_row(i, gl)) * D + 32 * hb + r] = acc[ib][i];
+    for (int i = 0; i < 16; ++i)
+      out[role * D * D + (32 * ib + d_row(i, gl)) * D + 32 * hb + r] = role == 0 ? acc[ib][i] : __builtin_amdgcn_ldexpf(acc[ib][i], e2);
   db1 += partner32(db1);
   if (role == 0 && gl == 0) out[2 * D * D + 32 * hb + r] = db1;
   // db2 over the 32 threads of a piece (the tiles are done with)
