@@ -71,11 +71,13 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const void* lds_ptr) {
 // barrier behind which other waves read it.
 // Written as assembly because the compiler, unable to tell the buffers apart, makes every later LDS
 // read wait for such a load; it does not count it either, which only makes its own vmcnt waits stricter.
+// The clobbers keep a value of its own out of M0 and accesses of the buffer on their side of the load; they
+// cost nothing (the code of k_phi_wgrad, the one user, is the same with and without).
 __device__ __forceinline__ void load_to_lds16(const void* src, unsigned char* lds) {
   typedef __attribute__((address_space(3))) unsigned char* lptr;
   const uint32_t at = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)lds)));
   // M0 holds the LDS address; one wait state between writing it and a load that uses it
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0", "memory");
 }
 __device__ __forceinline__ void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
