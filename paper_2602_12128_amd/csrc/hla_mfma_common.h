@@ -76,8 +76,9 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const void* lds_ptr) {
 __device__ __forceinline__ void load_to_lds16(const void* src, unsigned char* lds) {
   typedef __attribute__((address_space(3))) unsigned char* lptr;
   const uint32_t at = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)lds)));
+  uint32_t m0;  // never looked at: says that M0 is written (as a clobber of a reserved register it draws a warning)
   // M0 holds the LDS address; one wait state between writing it and a load that uses it
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0", "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off" : "={m0}"(m0) : "s"(at), "v"(src) : "memory");
 }
 __device__ __forceinline__ void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

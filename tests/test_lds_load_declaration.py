@@ -28,6 +28,6 @@ def test_load_to_lds_declares_m0_and_memory(tmp_path):
     calls = [line for line in open(ir) if "global_load_lds_dwordx4" in line and " asm " in line]
     assert calls
     for line in calls:
-        clobbers = set(re.findall(r"~\{(\w+)\}", line))
-        assert {"m0", "memory"} <= clobbers, line
+        changed = set(re.findall(r"[~=]\{(\w+)\}", line))  # outputs and clobbers
+        assert {"m0", "memory"} <= changed, line
         assert "sideeffect" in line
