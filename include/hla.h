@@ -215,9 +215,9 @@ hla_status hla_set_value_modulation(hla_handle* h, const hla_vmod_weights* maps,
  * every hla_backward OVERWRITES them on its stream; they must stay valid until that work has
  * completed.  Needs the modulation switched on (HLA_ERR_STATE otherwise); switching it off clears
  * the registration.  A backward over no tokens writes zeros.  Head dims other than 32, 64, 128 are
- * HLA_ERR_UNSUPPORTED.  The first registration allocates the workspace (per-token factors, 20
- * bytes per token-head and channel, and the partial sums; synchronous; HLA_ERR_ALLOC on
- * failure). */
+ * HLA_ERR_UNSUPPORTED.  The first registration allocates the workspace (per-token factors, 12
+ * bytes per token-head and channel, 4 on the matrix-core path, and the partial sums; synchronous;
+ * HLA_ERR_ALLOC on failure). */
 typedef struct {
   float* dW1;
   float* db1;

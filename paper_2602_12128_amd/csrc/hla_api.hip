@@ -482,9 +482,9 @@ hla_status hla_set_value_modulation_grads(hla_handle* hd, const hla_vmod_weight_
     float *part = nullptr, *rows = nullptr;
     size_t part_floats = static_cast<size_t>(kVmodWgradParts) * vmod_wgrad_part_floats(d);
     size_t row_floats = static_cast<size_t>(3) * hd->max_th * d;
-    if (hd->vmod_wpk != nullptr) {  // matrix-core handles: 16-bit factor arrays, per-workgroup partials
+    if (hd->vmod_wpk != nullptr) {  // matrix-core handles: a 16-bit factor array a map, per-workgroup partials
       part_floats = std::max(part_floats, static_cast<size_t>(vmod_mfma_partial_floats(hd)));
-      row_floats = std::max(row_floats, static_cast<size_t>(vmod_mfma_factor_floats(hd)));
+      row_floats = static_cast<size_t>(vmod_mfma_factor_floats(hd));
     }
     hla_status st = arena.alloc(&part, part_floats);
     if (st == HLA_OK) st = arena.alloc(&rows, row_floats);

@@ -199,3 +199,22 @@ def test_second_layer_gradient_follows_scales_that_grow():
             t = {k: v.flip(2).contiguous() for k, v in t.items()}
         gpu = pu.run_gpu(t, 3, 6, 1e-6, phi=phi, vmod=vm, vmod_weight_grads=True)
         pu.assert_vmod_weight_grad_parity(gpu["vwg"], ref["vwg"], 2e-2, f"modulation weight grads, growing scales, flip {flip}")
+
+
+@pytest.mark.parametrize("dtype,per_channel", [(torch.bfloat16, 4), (torch.float32, 12)])
+def test_modulation_weight_gradients_reserve_what_they_use(dtype, per_channel):
+    """Registering the gradients takes the per-token factors (4 bytes per token-head and channel on the
+    matrix-core path, 12 on the other) and at most 70 MB of partial sums."""
+    d, H, N = 128, 8, 32768
+    io = hla.HLA_BF16 if dtype == torch.bfloat16 else hla.HLA_F32
+    op = hla.HLA(head_dim=d, feature_dim=6, degree=3, io_dtype=io, phi_mode=hla.HLA_PHI_NONE, max_heads=H, max_tokens=N, max_seqs=1)
+    vm = [{k: v.cuda() for k, v in m.items()} for m in _vmod(1220, d, dtype)]
+    op.set_value_modulation(vm)
+    grads = [{"d" + k: torch.empty(v.shape, device="cuda") for k, v in m.items()} for m in vm]
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    op.set_value_modulation_grads(grads)
+    taken = before - torch.cuda.mem_get_info()[0]
+    op.destroy()
+    factors = per_channel * H * N * d
+    assert 0.9 * factors < taken < factors + (70 << 20), (taken, factors)
