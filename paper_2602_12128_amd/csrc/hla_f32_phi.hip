@@ -21,6 +21,7 @@ namespace {
 using namespace f32;
 
 constexpr int kTok = 64;
+constexpr int kMaxGridX = 1 << 22;  // a grid takes fewer than 2^32 threads in one direction
 
 // Phi(h) of the exact GELU, h Phi(h).  Below |h| = 1 it is 0.5 + h P(h^2), where an error of P shrinks with
 // h; beyond, Phi(-t) = 2^-(1 + P(t)) with a degree-8 minimax fit of P(t) = -log2(erfc(t / sqrt 2)) up to 5.9,
@@ -95,7 +96,8 @@ __device__ __forceinline__ void tile_coords(const PhiCall& c, int tile, int head
 }
 
 // ---- forward ------------------------------------------------------------------------------------
-// grid (tiles, 1 or H, 1 + F), block 256.  The sums run in the order of the input channels and of the
+// grid (tiles, 1 or H, 1 + F), block 256; with shared weights and more than kMaxGridX tiles, rows of that
+// many workgroups in y.  The sums run in the order of the input channels and of the
 // hidden units, one rounding per term: features near zero land on the same side of the ReLU as in
 // any other fp32 evaluation in that order.
 template <int D>
@@ -107,8 +109,10 @@ __global__ __launch_bounds__(256) void k_f32_phi_fwd(PhiCall c, View Q, View K, 
   const int r = lane % 32, hf = lane / 32;
   const Geom& g = c.g;
   const int m = blockIdx.z, hw = c.w.heads_w == 1 ? 0 : blockIdx.y;
+  const int tile = c.w.heads_w == 1 ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
+  if (tile >= c.tiles) return;
   int b, h, t0;
-  tile_coords(c, blockIdx.x, blockIdx.y, b, h, t0);
+  tile_coords(c, tile, blockIdx.y, b, h, t0);
   const int nt = min(kTok, g.N - t0);
   const int64_t mh = static_cast<int64_t>(m) * c.w.heads_w + hw;
   const float* W1 = c.w.W1 + mh * D * D;
@@ -464,7 +468,9 @@ PhiCall phi_call(const hla_handle* hd, const hla_call_args& a) {
 template <int D>
 hla_status fwd_d(hla_handle* hd, const hla_call_args& a) {
   const PhiCall c = phi_call(hd, a);
-  return launch(hd, "generic_phi_forward", &k_f32_phi_fwd<D>, dim3(c.tiles, c.w.heads_w == 1 ? 1 : a.H, 1 + c.g.F),
+  const bool shared = c.w.heads_w == 1;
+  const int gx = shared ? std::min(c.tiles, kMaxGridX) : c.tiles;
+  return launch(hd, "generic_phi_forward", &k_f32_phi_fwd<D>, dim3(gx, shared ? (c.tiles + gx - 1) / gx : a.H, 1 + c.g.F),
                 dim3(256), kTok * (D + 1) * sizeof(float), a.stream, c, a.Q, a.K, hd->feat);
 }
 
@@ -475,7 +481,7 @@ hla_status bwd_dn(hla_handle* hd, const hla_call_args& a) {
   const int heads = c.w.heads_w == 1 ? 1 : a.H;
   // without weight gradients a workgroup per tile; with them at most f32_phi_parts workgroups per list,
   // each of equally many tiles, as every one leaves a partial to be added up
-  int parts = c.tiles;
+  int parts = std::min(c.tiles, kMaxGridX);
   if (NM > 0) {
     const int most = std::max(1, f32_phi_parts(D) / heads);
     const int per = static_cast<int>((c.tiles + most - 1) / most);

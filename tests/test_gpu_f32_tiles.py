@@ -179,3 +179,26 @@ def test_gelu_and_its_slope_are_no_further_off_than_with_erf(spread):
         got = dX.cpu().reshape(H * N, d)[:, :dphi][side]
         want = sign * du * slope32[side]
         assert err(got) <= 1.02 * err(want), (m, err(got), err(want))
+
+
+def test_more_rows_than_a_grid_dimension_holds():
+    """2^24 (batch row, head) pairs of one token each: a workgroup of 256 threads per row is more than the 2^32
+    threads a grid takes in one direction.  The rows are alike, and so are the results."""
+    F, dphi, d = 1, 1, 32
+    gen = torch.Generator("cpu").manual_seed(3500)
+    row = {k: torch.randn(1, 1, 1, d, generator=gen).cuda() for k in ("Q", "K", "V", "dO")}
+    phi = wl.draw_phi_weights(torch.Generator("cpu").manual_seed(5), d, dphi, 1 + F, torch.float32)
+
+    def step(B, H):
+        op = hla.HLA(head_dim=d, feature_dim=dphi, degree=F, io_dtype=hla.HLA_F32, max_heads=H, max_tokens=B, max_seqs=B)
+        op.set_phi_weights([{k: v.cuda() for k, v in m.items()} for m in phi])
+        x = {k: v.expand(B, H, 1, d) for k, v in row.items()}
+        out = [torch.full((B, H, 1, d), 77.0, device="cuda") for _ in range(4)]
+        op.forward(x["Q"], x["K"], x["V"], out[0])
+        op.backward(x["Q"], x["K"], x["V"], out[0], x["dO"], *out[1:])
+        torch.cuda.synchronize()
+        op.destroy()
+        return out
+
+    for got, want in zip(step(4096, 4096), step(1, 1)):
+        assert bool((got == want).all())
