@@ -18,6 +18,10 @@ pytestmark = pytest.mark.gpu
     (2, 12, 128, 2, 129, None),
     (2, 12, 32, 1, 64, None),
     (3, 6, 32, 5, 8200, None),         # more tiles than partial states: runs of several tiles
+    (3, 6, 128, 5, 4100, None),        # the same at eight waves (254 partial states), in the two-factor
+    (2, 12, 128, 5, 2501, None),       # form (169) and with run-time monomials, an odd number of them (504)
+    (3, 5, 64, 5, 3301, None),         # or five row blocks (101)
+    (2, 16, 128, 5, 1001, None),
     (3, 5, 64, 2, 33, None),           # 35 monomials: an odd row count
     (1, 256, 32, 1, 31, None),         # 256 monomials of one factor
     (2, 16, 128, 2, 97, None),         # 136 monomials
@@ -72,6 +76,7 @@ def test_rows_off_sixteen_bytes(dtype):
     (2, 7, 64, 1, 1, 1),       # one token; odd d_phi
     (3, 6, 128, 1, 3, 129),
     (3, 6, 32, 1, 9, 4100),    # more tiles than partials: workgroups of several tiles
+    (3, 6, 128, 1, 5, 3301),   # and at eight waves
 ])
 def test_feature_map_tile_edges(F, dphi, d, B, H, N):
     t, phi = wl.make_raw_inputs(3200 + N + d, B, H, N, d, F, dphi, torch.float32)
