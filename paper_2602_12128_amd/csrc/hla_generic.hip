@@ -133,9 +133,8 @@ __global__ void k_dfeat_export(Geom g, const float* __restrict__ dfeat, View dQ,
 // ---- weight gradients of the feature maps: sum of the partials --------------------------------
 // Sum of the partial weight gradients of one (map, head) in a fixed order, times the scale of its
 // section, into the caller's arrays.  grid (ceil(floats SL / 256), 1+F, heads), block 256: SL slices of
-// the partials per element, sixteen loads in flight each.  What counts is the chain of memory round trips,
-// and with enough elements the traffic: 512 partials of 64 channels and 4 maps 18.8 us with one slice and
-// eight loads in flight, 8.4 with four slices; 64 partials of 128 channels 8.4, with four slices 9.5.
+// the partials per element, sixteen loads in flight each.  A workgroup is a chain of memory round trips, which
+// slices shorten; where the elements fill the card by themselves, they only add to what is in its way.
 struct WgradOut {
   float* dW1[kMaxF + 1];
   float* db1[kMaxF + 1];
@@ -564,7 +563,12 @@ hla_status weight_grads_reduce(hla_handle* hd, int nparts, int heads, float sW1,
     out.db2[m] = hd->wg_out[m].db2;
   }
   const int floats = static_cast<int>(hd->wg_part_floats);
-  const int sl = nparts > 128 ? 4 : 1;
+  // Four slices where one would leave compute units without a workgroup.  us with one / four slices, workgroups of
+  // one slice in brackets: 256 partials of 64 channels and 4 maps (76) 11.8 / 6.6, of 128 channels and 2
+  // maps (138) 12.3 / 10.2, 3 maps (213) 13.0 / 13.8, 4 maps (272) 13.9 / 16.5; 128 partials of 64 channels,
+  // 4 maps and 4 heads (304) 8.5 / 9.6.  With 64 partials and fewer either is within 0.7 of the other.
+  const int64_t groups = static_cast<int64_t>((floats + 255) / 256) * nm * heads;
+  const int sl = groups < 200 ? 4 : 1;
   return launch(hd, "phi_weight_grads_reduce", sl == 4 ? &k_wgrad_reduce<4> : &k_wgrad_reduce<1>,
                 dim3((floats * sl + 255) / 256, nm, heads), dim3(256), 0, s, hd->g.d, hd->g.dphi, nparts, static_cast<const float*>(hd->wg_partial), out,
                 sW1, sb1, sW2, sb2);
