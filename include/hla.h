@@ -46,7 +46,7 @@ typedef enum { HLA_F32 = 0, HLA_BF16 = 1 } hla_dtype;
 
 /* HLA_PHI_MLP : Q and K hold raw head vectors [.., d]; the library applies the feature maps of
  *               App. A.1 (Linear d->d, GELU, Linear d->d_phi, ReLU) — Alg. 1 Step 4.  GELU is the
- *               exact erf form x Phi(x) on the generic path; the MFMA path evaluates a polynomial
+ *               exact form x Phi(x) to fp32 rounding on the generic path; the MFMA path evaluates a polynomial
  *               fit of it in packed fp16 (|error| <= 5.2e-3 absolute, rms 5e-4 for standard-normal
  *               pre-activations, below the rounding of a bf16 hidden layer), and needs
  *               |pre-activation| < 2.6e5.
@@ -60,7 +60,8 @@ typedef enum { HLA_PHI_MLP = 0, HLA_PHI_NONE = 1 } hla_phi_mode;
  * or F = 2 with d_phi = 12. */
 typedef enum {
   HLA_PATH_AUTO = 0,
-  HLA_PATH_GENERIC = 1, /* fp32 vector-ALU kernels over the literal d_phi^F state; any supported shape */
+  HLA_PATH_GENERIC = 1, /* fp32 features and state on the fp32 matrix cores; any supported shape (the causal
+                           variant: a token-by-token scan over the literal d_phi^F state) */
   HLA_PATH_MFMA = 2     /* bf16 matrix-core kernels; HLA_ERR_UNSUPPORTED if the shape has none */
 } hla_kernel_path;
 

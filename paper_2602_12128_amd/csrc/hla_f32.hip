@@ -10,8 +10,9 @@
 // features and rows are staged in LDS; lane = token evaluates monomials and chain rule, the waves
 // taking a share of the monomials each; the four products per token (C += S^T V, O = Qm C,
 // X = dO C^T, ..) are 32x32 MFMA tiles dealt out to the waves, both operands from LDS.  An fp32
-// MFMA holds the matrix pipe 64 cycles for 512 bytes of operands, an eighth of what LDS delivers in
-// that time, so plain LDS operands keep the pipe fed without register blocking.
+// MFMA holds the matrix pipe 64 cycles for 512 bytes of operands, a sixteenth of what LDS delivers in
+// that time (a quarter with all four SIMDs at it), so plain LDS operands keep the pipe fed without
+// register blocking.
 #include <algorithm>
 
 #include "hla_f32_common.h"

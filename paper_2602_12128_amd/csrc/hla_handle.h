@@ -191,6 +191,7 @@ hla_status convert_weights_to_f32(hla_handle* hd, const hla_phi_weights* maps, h
 // scales the four sections and writes the caller's arrays.
 hla_status phi_weight_grads(hla_handle* hd, const hla_call_args& a);
 hla_status mfma_phi_weight_grads(hla_handle* hd, const hla_call_args& a);
+int64_t mfma_phi_wgrad_parts(const hla_handle* hd);
 hla_status weight_grads_reduce(hla_handle* hd, int nparts, int heads, float sW1, float sb1, float sW2,
                                float sb2, hipStream_t s);
 

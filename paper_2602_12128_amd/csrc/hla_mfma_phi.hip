@@ -8,9 +8,9 @@
 //                                    memory in operand order
 //   u^T[d_phi x 32]  = W2^T g^T      B = GELU(hidden) packed straight from the accumulators
 // and backward   dg^T = W2 du^T,  dh = dg * GELU'(hidden),  dx^T = W1 dh^T  (A = the same LDS copy
-// of W1^T, transpose reads).  The weights of a head stay resident in LDS while the workgroup
-// works through its tiles (first the query map's, then the key maps'); each wave streams its own
-// 32-token tiles, and two (backward) or three (forward) waves
+// of W1^T, transpose reads).  The weights of all maps (of one map where tiles are few, see forward_t)
+// stay resident in LDS while the workgroup works through its tiles, the key tiles first; each wave
+// takes 32-token tiles from the workgroup's list, and two (backward) or three (forward) waves
 // share a SIMD so that one wave's GELU arithmetic overlaps the others' matrix and LDS work.
 #include "hla_handle.h"
 #include "hla_mfma_common.h"
@@ -405,7 +405,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_phi_fwd(Geom g, View Q, View K,
 // dX = sum over the maps of W1 (GELU'(h) * (W2 du)), with du = d(feature) where the ReLU was open (the
 // form in which the feature-gradient workspace arrives).  Hidden activations are recomputed.  All
 // maps stay in LDS; the waves of a workgroup take its 32-token tiles from a counter as in the forward.
-// Bound: power, as the forward (1.9 GHz), with 470 MB of traffic beside it.  With fixed shares and the
+// Bound: the clock falls as in the forward, but vector ALU and matrix pipe together are busy only
+// 77 % of the cycles (forward 89 %), 38 % of the matrix time has vector work beside it (57 %), and a wave
+// waits to issue 37 % and sits in s_waitcnt 21 % of its life: two waves per SIMD do not cover each other's
+// LDS transpose reads and chains, with 470 MB of traffic beside it.  With fixed shares and the
 // weights swapped half way: 150 us at 12 heads x 32760 tokens x 128 channels, 70 at 12600 (a third
 // round of tiles for some waves only), 129 in the two-factor form at 32760; now 138, 60 and 113 us.
 template <int D, int F, int WAVES, int DPH>
@@ -1006,6 +1009,8 @@ hla_status allow_lds(K kernel, int bytes) {
              : HLA_ERR_HIP;
 }
 
+constexpr int kUnits = 256;  // compute units of the card
+
 // One workgroup per compute unit in total.  Shared weights: a flat grid over all tiles; per-head
 // weights: (x, H, B) with x workgroups per (batch row, head).
 dim3 phi_grid(const hla_handle* hd, int waves) {
@@ -1014,10 +1019,10 @@ dim3 phi_grid(const hla_handle* hd, int waves) {
   if (hd->phi.heads_w == 1) {
     const int64_t total = static_cast<int64_t>(tiles) * g.B * g.H;
     const int64_t want = (total + waves - 1) / waves;
-    return dim3(static_cast<unsigned>(want < 256 ? (want < 1 ? 1 : want) : 256), 1, 1);
+    return dim3(static_cast<unsigned>(want < kUnits ? (want < 1 ? 1 : want) : kUnits), 1, 1);
   }
   const int units = g.B * g.H;
-  int gx = 256 / units;  // rounding down keeps the whole grid resident in one round
+  int gx = kUnits / units;  // rounding down keeps the whole grid resident in one round
   const int need = (tiles + waves - 1) / waves;
   if (gx > need) gx = need;
   return dim3(gx < 1 ? 1 : gx, g.H, g.B);
@@ -1043,7 +1048,7 @@ hla_status forward_t(hla_handle* hd, const hla_call_args& a) {
   const int64_t tiles = static_cast<int64_t>((g.N + 31) / 32) * g.B * g.H;
   const int split = hd->phi.heads_w == 1 && tiles < kSplitTiles;
   dim3 grid = phi_grid(hd, kWavesF);
-  if (split) grid = dim3(static_cast<unsigned>(std::min<int64_t>(256 / (1 + F), tiles)), 1 + F, 1);
+  if (split) grid = dim3(static_cast<unsigned>(std::min<int64_t>(kUnits / (1 + F), tiles)), 1 + F, 1);
   return launch(hd, "mfma_phi_forward", k_phi_fwd<D, F, kWavesF, DPH>, grid, dim3(kWavesF * 64),
                 SM::total(split ? 1 : 1 + F, kWavesF), a.stream, g, a.Q, a.K, wpk, hd->phi.heads_w, split, hd->feat);
 }
@@ -1059,12 +1064,14 @@ hla_status backward_t(hla_handle* hd, const hla_call_args& a) {
   return HLA_OK;
 }
 
-constexpr int kWavesW = 4;  // two workgroups per compute unit: their barriers leave each other alone
+// two workgroups per compute unit: their barriers leave each other alone
+constexpr int kWavesW = 4, kGridW = 2 * kUnits;
+constexpr int wgrad_groups(int d) { return kWavesW / (d / 32); }  // wave groups of a workgroup, a partial sum each
 
 template <int D, int DPH>
 hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
   using SM = WgSmem<D>;
-  constexpr int TH = kWavesW / (D / 32);
+  constexpr int TH = wgrad_groups(D);
   constexpr int lds = TH * SM::kBufs * SM::kBuf;
   Geom g = hd->g;
   const unsigned char* wpk = static_cast<const unsigned char*>(hd->path_ws) + hd->w_packed_off;
@@ -1072,8 +1079,8 @@ hla_status weight_grads_t(hla_handle* hd, const hla_call_args& a) {
   const bool shared = hd->phi.heads_w == 1;
   const int heads = shared ? 1 : g.H;
   const int64_t tiles = static_cast<int64_t>(shared ? g.B * g.H : g.B) * ((g.N + SM::kTok - 1) / SM::kTok);
-  // one workgroup per compute unit in total, each with at least one tile per wave group
-  int64_t nblk = 512 / (static_cast<int64_t>(nm) * heads);
+  // at most kGridW workgroups in total (but one per map and head), each with at least one tile per wave group
+  int64_t nblk = kGridW / (static_cast<int64_t>(nm) * heads);
   if (nblk > (tiles + TH - 1) / TH) nblk = (tiles + TH - 1) / TH;
   if (nblk < 1) nblk = 1;
   const int64_t nparts = nblk * TH;
@@ -1090,7 +1097,7 @@ template <int D, int F, int DPH>
 hla_status prepare_t() {
   HLA_TRY(allow_lds(&k_phi_fwd<D, F, kWavesF, DPH>, PhiSmem<D>::total(1 + F, kWavesF)));
   HLA_TRY(allow_lds(&k_phi_bwd<D, F, kWavesB, DPH>, PhiSmem<D, true, (DPH <= 8 ? 8 : 16)>::total(1 + F, kWavesB)));
-  return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, kWavesW / (D / 32) * WgSmem<D>::kBufs * WgSmem<D>::kBuf);
+  return allow_lds(&k_phi_wgrad<D, kWavesW, DPH>, wgrad_groups(D) * WgSmem<D>::kBufs * WgSmem<D>::kBuf);
 }
 
 }  // namespace
@@ -1109,6 +1116,11 @@ hla_status mfma_phi_weight_grads(hla_handle* hd, const hla_call_args& a) {
   if (!mfma_phi_supported(hd)) return HLA_ERR_UNSUPPORTED;
   if (hd->g.F == 3) return hd->g.d == 128 ? weight_grads_t<128, 6>(hd, a) : weight_grads_t<64, 6>(hd, a);
   return hd->g.d == 128 ? weight_grads_t<128, 12>(hd, a) : weight_grads_t<64, 12>(hd, a);
+}
+
+// most partial weight gradients of a call, all maps and heads together
+int64_t mfma_phi_wgrad_parts(const hla_handle* hd) {
+  return wgrad_groups(hd->g.d) * std::max<int64_t>(kGridW, static_cast<int64_t>(1 + hd->g.F) * hd->cfg.max_heads);
 }
 
 size_t mfma_phi_packed_bytes(const hla_handle* hd) {

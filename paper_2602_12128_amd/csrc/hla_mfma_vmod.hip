@@ -815,7 +815,7 @@ struct VWgSmem {
   static constexpr int kTotal = kGroups * 2 * kBuf;
   static constexpr int kPart = 2 * D * D + 2 * D;              // floats of a partial
 };
-constexpr int kWgBlocks = 128;  // workgroups per map: one per compute unit
+constexpr int kWgBlocks = 128;  // workgroups per map; with two maps one per compute unit of the card's 256
 
 template <int D>
 __global__ __launch_bounds__(512, 2) void k_vmod_wgrad(Geom g, const unsigned char* __restrict__ wpk, View Tin, View V,

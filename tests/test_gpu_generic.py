@@ -1,5 +1,5 @@
-"""GPU parity of the generic (fp32 vector-ALU, literal d_phi^F state) path against the CPU
-oracle, element by element, through the C ABI.  Sizes span several tiles and chunks with
+"""GPU parity of the generic path (fp32 matrix cores, any supported form) against the CPU
+oracle, element by element, through the C ABI.  Sizes span several tiles and runs of tiles with
 ragged tails; edge cases cover empty input, packed sequences and error codes."""
 import ctypes
 
@@ -25,7 +25,7 @@ def test_config1_tiny_forward_fp32_both_oracle_routes():
 
 @pytest.mark.parametrize("F,dphi,d,N,kind", [
     (3, 6, 32, 300, "halfnormal"),
-    (3, 6, 128, 1100, "lognormal"),   # crosses the 1024-token chunk boundary
+    (3, 6, 128, 1100, "lognormal"),   # 18 tiles a head, the last one ragged
     (2, 12, 64, 257, "sparse"),
     (1, 16, 32, 65, "halfnormal"),
     (4, 4, 64, 130, "halfnormal"),
