@@ -232,7 +232,8 @@ hla_status hla_set_value_modulation_grads(hla_handle* h, const hla_vmod_weight_g
 /* hla_forward for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  No handle: the workspace (features, chunk
  * partial states, the reduced state, token tables) lives in a static device array of
- * HLA_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until the process ends.  The
+ * HLA_STATIC_SCRATCH_BYTES inside the library (on the generic path the partial states in a second one
+ * of half its size), one copy per GPU, held until the process ends.  The
  * call allocates nothing on the device, copies nothing from the host and never synchronises; it
  * runs the same kernels as hla_forward and returns the same bits.
  *   - HLA_PHI_NONE only (Q and K hold features, see hla_phi_mode); dense batches only (every

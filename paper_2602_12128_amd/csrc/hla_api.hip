@@ -7,9 +7,16 @@
 #include "hla_handle.h"
 
 // Workspace of hla_forward_static: one copy per GPU, for as long as the process lives.  In host
-// code this name is only a handle for hipGetSymbolAddress; the address kernels and fills use is
+// code these names are only handles for hipGetSymbolAddress; the address kernels and fills use is
 // the one that call returns, kept per device in g_static below.
 static __device__ __align__(256) unsigned char scratch[HLA_STATIC_SCRATCH_BYTES];
+
+// The generic path's partial states have a place of their own: their number is chosen for the card, not for
+// the call (8 MiB of them, up to twice that where the heads do not divide it), and must not decide which
+// calls fit the array above.  More than this only a batch of many sequences needs, whose states alone
+// would then fill half of that array.
+constexpr size_t kStaticPartialBytes = 16u << 20;
+static __device__ __align__(256) unsigned char partial_scratch[kStaticPartialBytes];
 
 namespace hla {
 
@@ -119,25 +126,22 @@ namespace {
 
 // Where a handle's device workspace comes from: hipMalloc (one allocation per array, owned by the
 // handle), or consecutive 256-byte aligned pieces of a block of device memory that is not the
-// handle's (base != nullptr; nothing is allocated and nothing will be freed).  measure: only `used`,
-// what such a block has to hold, is added up; the pointers stay null.
+// handle's (base != nullptr; nothing is allocated and nothing will be freed).
 struct Arena {
   unsigned char* base = nullptr;
   size_t cap = 0;
   size_t used = 0;
-  bool measure = false;
   template <typename T>
   hla_status alloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
     const size_t bytes = count * sizeof(T);
-    if (base == nullptr && !measure)
+    if (base == nullptr)
       return hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess ? HLA_OK : HLA_ERR_ALLOC;
     const size_t at = (used + 255) / 256 * 256;
-    used = at + bytes;
-    if (measure) return HLA_OK;
-    if (used > cap) return HLA_ERR_TOO_LARGE;
+    if (at + bytes > cap) return HLA_ERR_TOO_LARGE;
     *p = reinterpret_cast<T*>(base + at);
+    used = at + bytes;
     return HLA_OK;
   }
 };
@@ -255,8 +259,9 @@ hla_status plan_handle(hla_handle* hd, const hla_config& c) {
 }
 
 // The device arrays the plan asked for.  forward_only leaves out what only a backward touches
-// (feature gradients, the state gradient, the generic path's per-token scratch).
-hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only) {
+// (feature gradients, the state gradient, the generic path's per-token scratch).  partials: where the partial
+// states go if they fit there.
+hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only, Arena* partials = nullptr) {
   const hla_config& c = hd->cfg;
   const int64_t feat_rows = (hd->max_th + 31) / 32 * 32;  // whole 32-token groups for the tiled layout
   HLA_TRY(arena.alloc(&hd->feat, feat_rows * hd->g.nfeat));
@@ -265,7 +270,9 @@ hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only) {
   if (!forward_only) HLA_TRY(arena.alloc(&hd->yhat, hd->yhat_floats));
   HLA_TRY(arena.alloc(&hd->state, hd->max_units * hd->state_stride));
   if (!forward_only) HLA_TRY(arena.alloc(&hd->dstate, hd->max_units * hd->state_stride));
-  HLA_TRY(arena.alloc(&hd->partial, hd->max_chunks * c.max_heads * hd->state_stride));
+  const size_t partial_floats = static_cast<size_t>(hd->max_chunks * c.max_heads * hd->state_stride);
+  if (partials == nullptr || partials->alloc(&hd->partial, partial_floats) != HLA_OK)
+    HLA_TRY(arena.alloc(&hd->partial, partial_floats));
   if (hd->path_ws_bytes > 0) {
     char* p = nullptr;
     HLA_TRY(arena.alloc(&p, hd->path_ws_bytes));
@@ -287,34 +294,9 @@ hla_status allocate_workspace(hla_handle* hd, Arena& arena, bool forward_only) {
   return HLA_OK;
 }
 
-// Plan of the static forward for the exact sizes in `c`.  The generic path's partial states are a matter of
-// speed above one per (sequence, head): where all of them would not fit, as many as do.
-hla_status plan_static(hla_handle* hd, const hla_config& c) {
-  HLA_TRY(plan_handle(hd, c));
-  if (hd->path != HLA_PATH_GENERIC) return HLA_OK;
-  Arena arena;
-  arena.measure = true;
-  HLA_TRY(allocate_workspace(hd, arena, /*forward_only=*/true));
-  if (arena.used <= HLA_STATIC_SCRATCH_BYTES) return HLA_OK;
-  // whole chunks, and what the alignment of the arrays behind the partial states can take back
-  const int64_t over = static_cast<int64_t>(arena.used - HLA_STATIC_SCRATCH_BYTES) + 1024;
-  const int64_t chunk = static_cast<int64_t>(c.max_heads) * hd->state_stride * 4;
-  hd->max_chunks = std::max<int64_t>(hd->max_chunks - (over + chunk - 1) / chunk, c.max_seqs);
-  return HLA_OK;
-}
-
 bool bad_view(const hla_tensor& t) { return t.ptr == nullptr; }
 
 }  // namespace
-
-int64_t hla::static_partial_chunks(const hla_config& cfg, int32_t B, int32_t H, int32_t N) {
-  hla_config c = cfg;
-  c.max_heads = H;
-  c.max_tokens = static_cast<int64_t>(B) * N;
-  c.max_seqs = B;
-  hla_handle plan{};
-  return plan_static(&plan, c) == HLA_OK ? plan.max_chunks : c.max_seqs;
-}
 
 extern "C" {
 
@@ -624,6 +606,7 @@ __global__ void k_fill_zero(uint32_t* __restrict__ p, int64_t words) {
 constexpr int kMaxDevices = 64;
 struct StaticSlot {
   unsigned char* ptr = nullptr;  // device address of this GPU's copy of `scratch`
+  unsigned char* partials = nullptr;  // and of `partial_scratch`
   hla_handle* hd = nullptr;      // host-side bookkeeping; its device pointers point into `scratch`
   bool planned = false;          // hd is laid out for `cfg`
   hla_config cfg{};
@@ -659,22 +642,28 @@ hla_status hla_forward_static(const hla_config* config, int32_t B, int32_t H, in
   if (sl.ptr == nullptr) {  // first call on this device
     void* p = nullptr;
     HLA_HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    if (p == nullptr) return HLA_ERR_HIP;
+    void* q = nullptr;
+    HLA_HIP_TRY(hipGetSymbolAddress(&q, HIP_SYMBOL(partial_scratch)));
+    if (p == nullptr || q == nullptr) return HLA_ERR_HIP;
     hla_handle* hd = new (std::nothrow) hla_handle();
     if (hd == nullptr) return HLA_ERR_ALLOC;
     sl.hd = hd;
     sl.ptr = static_cast<unsigned char*>(p);
+    sl.partials = static_cast<unsigned char*>(q);
   }
   hla_handle* hd = sl.hd;
   if (!sl.planned || !same_config(sl.cfg, c)) {
     sl.planned = false;
     *hd = hla_handle();
     hd->borrowed_ws = true;
-    HLA_TRY(plan_static(hd, c));
-    Arena arena;
+    HLA_TRY(plan_handle(hd, c));
+    Arena arena, partials;
     arena.base = sl.ptr;
     arena.cap = HLA_STATIC_SCRATCH_BYTES;
-    HLA_TRY(allocate_workspace(hd, arena, /*forward_only=*/true));  // HLA_ERR_TOO_LARGE: does not fit
+    partials.base = sl.partials;
+    partials.cap = kStaticPartialBytes;
+    // HLA_ERR_TOO_LARGE: does not fit
+    HLA_TRY(allocate_workspace(hd, arena, /*forward_only=*/true, hd->path == HLA_PATH_GENERIC ? &partials : nullptr));
     if (hd->path == HLA_PATH_MFMA) HLA_TRY(mfma_prepare_kernels(hd));
     // the array keeps what the last call left: padding entries of the packed operands must read
     // as zero (a fill kernel rather than a memset node, so that the call can be captured)

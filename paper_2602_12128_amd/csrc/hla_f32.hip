@@ -765,11 +765,8 @@ hla_status runs_table(hla_handle* hd, const hla_call_args& a, hla_token_table** 
   // the same sequences and heads as the last call's (its backward, the next step): the same runs
   if (hd->tables[0].valid && hd->runs_heads == a.H) return get_table(hd, 0, hd->tables[0].block_tokens, a.stream, out);
   const int tok = tok_of(hd);
+  const int64_t cap = max_partials(hd);
   const int nseq = a.num_seqs;
-  int64_t cap = max_partials(hd);
-  // a call that the static forward also takes cuts its tokens into the same runs there: same bits
-  if (hd->cfg.phi_mode == HLA_PHI_NONE && !a.packed)
-    cap = std::min(cap, static_partial_chunks(hd->cfg, a.B, a.H, a.N) * a.H);
   auto count = [&](int64_t per) {  // runs per head with `per` tiles each
     const int64_t blk = per * tok;
     if (!a.packed) return static_cast<int64_t>(a.B) * ((a.N + blk - 1) / blk);

@@ -136,8 +136,6 @@ hla_status mfma_prepare_kernels(const hla_handle* hd);
 hla_status generic_prepare_kernels(const hla_handle* hd, hipStream_t s);
 // Non-causal operator of the generic path (hla_f32.hip).
 hla_status f32_workspace_plan(hla_handle* hd);
-// Partial states per head of the static forward's layout for a dense call of this shape on the generic path.
-int64_t static_partial_chunks(const hla_config& cfg, int32_t B, int32_t H, int32_t N);
 hla_status f32_prepare_kernels(const hla_handle* hd, hipStream_t s);
 // Feature maps of the generic path and their gradients (hla_f32_phi.hip).  f32_phi_parts: most partial
 // weight gradients of a map; two workgroups per compute unit at d <= 64, one at d = 128.

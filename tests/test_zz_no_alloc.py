@@ -66,12 +66,12 @@ def test_static_forward_reads_features_in_place(F, dphi, d):
     (2, 12, 64, 12, 14565),
     (2, 12, 32, 12, 16426),
     (1, 6, 128, 12, 50349),
-    (1, 256, 128, 1, 15200),   # room for 16 of 63 partial states
+    (1, 256, 128, 1, 15200),
     (3, 5, 64, 12, 23541),     # an odd number of monomials: states on 4-byte addresses
 ])
 def test_static_forward_takes_calls_that_fill_the_array(F, dphi, d, H, N):
-    """fp32 calls that fit the static array with as many partial states as the sequence has thousands of
-    tokens: what the kernels would like beyond that gives way, in the handle's forward of that shape too."""
+    """fp32 calls that fill the static array with features and states: the partial states, of which the kernels
+    want several MiB whatever the form, have a place of their own."""
     t = wl.make_feature_inputs(980 + F, 1, H, N, d, F, dphi, torch.float32)
     got = _static_forward(t, F, dphi, io_dtype=hla.HLA_F32)
     want = pu.run_gpu(t, F, dphi, 1e-6, backward=False)
